@@ -24,6 +24,7 @@
 #include "../common.h"
 #include "bf16.h"
 #include "tgauss.h"
+#include "lds_tr.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -772,11 +773,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_pair_f(RProb p0, RProb p1, in
 // An operand is read in one of two orientations:
 //  - plain (k-contiguous rows): four lanes cover a row's 64 bytes of a chunk;
 //  - transposed (rows contiguous, k strided -- dY and X of a weight gradient, W
-//    of an input gradient): four lanes cover 32 rows at one k, and the chunk is
-//    written transposed into the wave's LDS tile.
-// Fragments are then read from the LDS tile; a transposed operand's tile swizzles
-// its 16-byte k groups by row (group g of row c sits at g ^ (c / 8) mod 4), so the
-// transposing stores of the 64 lanes spread over the banks.  DIRECT (both operands plain, short K
+//    of an input gradient): four lanes cover 32 rows at one k.
+// Both go to the wave's LDS tile line by line with 16-byte stores; a plain operand's
+// fragments are 16-byte reads of its rows, a transposed one's are transposing reads
+// (lds_tr.h).  Storing a transposed operand element by element into a [row][k] tile
+// instead took 16 two-byte stores per lane and chunk, and 6.7 / 7.1 us against
+// 6.1 / 6.3 for 2 x 512^3 with one / both operands transposed (both plain: 6.0), and
+// 14.8 / 15.5 against 14.2 / 12.0 for 2 x 512x512x2000.
+// DIRECT (both operands plain, short K
 // ranges): lane (li, lq) loads its fragment (rows li and 16 + li, k = 8 lq ..
 // 8 lq + 7 of the chunk) straight from memory.
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
@@ -796,11 +800,15 @@ constexpr int kHMaxC = 4;   // chunks of a wave in flight at once
 constexpr int kHLdt = 40;   // row stride of a wave's LDS tile (elements)
 constexpr int kHTile = 32 * kHLdt;
 
-// element (c, k) of a wave's tile; a transposed operand's tile swizzles its 16-byte k groups
+// fragment i (rows 16 i .. 16 i + 15) of a chunk in a wave's tile: [row][k] for a plain
+// operand, [k][row] for a transposed one (read back transposed)
 template <bool T>
-__device__ __forceinline__ int hpos(int c, int k) {
-  if constexpr (T) return c * kHLdt + ((((k >> 3) ^ (c >> 3)) & 3) << 3) + (k & 7);
-  return c * kHLdt + k;
+__device__ __forceinline__ bf16x8 hfrag(const uint16_t* tile, int i, int li, int lq) {
+  if constexpr (T) {
+    const uint16_t* p = tile + (8 * lq + (li >> 2)) * kHLdt + 16 * i + 4 * (li & 3);
+    return lds_tr8(p, p + 4 * kHLdt);
+  }
+  return *reinterpret_cast<const bf16x8*>(tile + (16 * i + li) * kHLdt + 8 * lq);
 }
 
 // elements k >= kend of a loaded group starting at kq read as zero
@@ -851,23 +859,12 @@ __device__ __forceinline__ void hmask_chunk(u4v (&v)[2], int k0, int kend, int l
   }
 }
 
-// a loaded chunk into the wave's LDS tile, as [row][k]
-template <bool T>
+// a loaded chunk into the wave's LDS tile: lines (rows, or k of a transposed operand)
+// of 32 elements in the order they were loaded
 __device__ __forceinline__ void hstage(const u4v (&v)[2], uint16_t* tile, int lane) {
-  const int q = lane & 3;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int r = 16 * j + (lane >> 2);   // plain: the row; transposed: the k
-    if constexpr (T) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const unsigned w = v[j][e >> 1];
-        tile[hpos<true>(8 * q + e, r)] = (uint16_t)((e & 1) ? (w >> 16) : (w & 0xffffu));
-      }
-    } else {
-      *reinterpret_cast<u4v*>(tile + hpos<false>(r, 8 * q)) = v[j];
-    }
-  }
+  for (int j = 0; j < 2; ++j)
+    *reinterpret_cast<u4v*>(tile + (16 * j + (lane >> 2)) * kHLdt + 8 * (lane & 3)) = v[j];
 }
 
 template <bool DIRECT>
@@ -941,8 +938,8 @@ __device__ __forceinline__ void gemm_tile_h(const HMat& fa, const HMat& fb, cons
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) {
           if (g + h + c2 < nch) {
-            hstage<TA>(ra[h + c2], wt + (2 * c2) * kHTile, lane);
-            hstage<TB>(rb[h + c2], wt + (2 * c2 + 1) * kHTile, lane);
+            hstage(ra[h + c2], wt + (2 * c2) * kHTile, lane);
+            hstage(rb[h + c2], wt + (2 * c2 + 1) * kHTile, lane);
           }
         }
         lds_wave_sync();
@@ -952,8 +949,8 @@ __device__ __forceinline__ void gemm_tile_h(const HMat& fa, const HMat& fb, cons
             bf16x8 a[2], b[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-              a[i] = *reinterpret_cast<const bf16x8*>(wt + (2 * c2) * kHTile + hpos<TA>(16 * i + li, 8 * lq));
-              b[i] = *reinterpret_cast<const bf16x8*>(wt + (2 * c2 + 1) * kHTile + hpos<TB>(16 * i + li, 8 * lq));
+              a[i] = hfrag<TA>(wt + (2 * c2) * kHTile, i, li, lq);
+              b[i] = hfrag<TB>(wt + (2 * c2 + 1) * kHTile, i, li, lq);
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i)

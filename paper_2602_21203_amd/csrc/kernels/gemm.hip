@@ -867,6 +867,10 @@ __device__ __forceinline__ void hstage(const u4v (&v)[2], uint16_t* tile, int la
     *reinterpret_cast<u4v*>(tile + (16 * j + (lane >> 2)) * kHLdt + 8 * (lane & 3)) = v[j];
 }
 
+}  // namespace sq
+#include "gemm_big.h"
+namespace sq {
+
 template <bool DIRECT>
 constexpr int hgemm_lds_bytes() {
   constexpr int RED_BYTES = 4 * kTile * (kTile + 1) * 4;
@@ -1007,6 +1011,58 @@ __global__ __launch_bounds__(kThreads) void k_gemm_pair_h(HProb p0, HProb p1, in
   }
 }
 
+// The pairs with problem 0 on the 64 x 64 tile: a layer's input gradient, with the
+// weight gradient (few tiles, a long contraction: the 32 x 32 tile's split of K over
+// its waves) in the workgroups before it, so that those longer chains start first; or
+// two forward products.  t1: problem 1's workgroups.
+template <bool BF16, int KA, int KB>
+__global__ __launch_bounds__(kThreads, 2) void k_gemm_pair_big(RProb p0, RProb p1, int t1) {
+  constexpr int L0 = BigLds<BF16>::BYTES, L1 = gemm_lds_bytes<BF16, 0, 0>();
+  __shared__ __attribute__((aligned(16))) char lds[L0 > L1 ? L0 : L1];
+  const int b = blockIdx.x;
+  if (b < t1) {
+    const StPart none{nullptr, 0, 0, 1};
+    gemm_tile<BF16, 0, 0, StMat, false>(p1.a, p1.b, p1.st, none, p1.M, p1.N, p1.K, p1.K, b % p1.gx,
+                                        (b / p1.gx) % p1.gy, b / (p1.gx * p1.gy), lds);
+  } else {
+    int bx, by, bz;
+    tile_of(b - t1, p0.gx, p0.gy, ((int)gridDim.x - t1) / (p0.gx * p0.gy), bx, by, bz);
+    big_tile_f<BF16, KA, KB>(p0.a, p0.b, p0.st, p0.M, p0.N, p0.K, bx, by, bz, lds);
+  }
+}
+
+__global__ __launch_bounds__(kThreads, 3) void k_gemm_pair_big_h(HProb p0, HProb p1, int t1) {
+  constexpr int L0 = BigLds<true>::BYTES, L1 = hgemm_lds_bytes<false>();
+  __shared__ __attribute__((aligned(16))) char lds[L0 > L1 ? L0 : L1];
+  const int b = blockIdx.x;
+  if (b < t1) {
+    gemm_tile_h<false, true, true, false, StMat>(p1.a, p1.b, p1.st, p1.M, p1.N, p1.K, b % p1.gx, (b / p1.gx) % p1.gy,
+                                                 b / (p1.gx * p1.gy), lds);
+  } else {
+    int bx, by, bz;
+    tile_of(b - t1, p0.gx, p0.gy, ((int)gridDim.x - t1) / (p0.gx * p0.gy), bx, by, bz);
+    big_tile_h<false, true>(p0.a, p0.b, p0.st, p0.M, p0.N, p0.K, bx, by, bz, lds);
+  }
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kThreads, BF16 ? 4 : 3) void k_gemm_pair_big_f(RProb p0, RProb p1, int t1) {
+  __shared__ __attribute__((aligned(16))) char lds[BigLds<BF16>::BYTES];
+  const bool one = (int)blockIdx.x < t1;
+  const RProb& p = one ? p1 : p0;
+  const int b = one ? blockIdx.x : blockIdx.x - t1;
+  big_tile_f<BF16, kBigRow, kBigRow>(p.a, p.b, p.st, p.M, p.N, p.K, b % p.gx, (b / p.gx) % p.gy, b / (p.gx * p.gy),
+                                     lds);
+}
+
+__global__ __launch_bounds__(kThreads, 4) void k_gemm_pair_big_hf(HProb p0, HProb p1, int t1) {
+  __shared__ __attribute__((aligned(16))) char lds[BigLds<true>::BYTES];
+  const bool one = (int)blockIdx.x < t1;
+  const HProb& p = one ? p1 : p0;
+  const int b = one ? blockIdx.x : blockIdx.x - t1;
+  big_tile_h<false, false>(p.a, p.b, p.st, p.M, p.N, p.K, b % p.gx, (b / p.gx) % p.gy, b / (p.gx * p.gy), lds);
+}
+
 // rows of a small matrix copied into another's columns, and into its bfloat16 copy
 // when it has one (the unfused policy head's second action copy)
 __global__ void k_copy_rows(const float* __restrict__ src, int cols, int rows, float* __restrict__ dst, long long ld,
@@ -1081,6 +1137,64 @@ static int rkind(const MatArg& a) {
 static RMat rmat(const MatArg& m) { return RMat{m.p, m.lr, m.lk, m.sz, m.alt, m.zalt, m.zdiv, m.kp, m.kalt}; }
 static StMat stmat(const OutArg& c) {
   return StMat{c.p, c.ld, c.sz, c.bias, c.bias_sz, c.accumulate, c.relu, c.bias_alt, c.bias_zalt};
+}
+
+// Whether a product takes the 64 x 64 tile: enough of those tiles, FP32 operands at
+// least one a compute unit, bfloat16 copies (whose 32 x 32 form reads half the bytes
+// and keeps its lead longer) about two.  Measured, 32 x 32 -> 64 x 64 tile, us:
+//   FP32 operands, FP32 / bfloat16 mode   copies
+//   128 tiles (2 x 512^3)           10.9 -> 16.3   6.8 -> 9.4     6.0 -> 8.5
+//   256 tiles (4 x 512^3)           19.4 -> 17.3  11.1 -> 9.9     8.3 -> 8.9
+//   512 tiles (2 x 2048x512x512)    36.4 -> 26.9  20.7 -> 13.1   14.1 -> 11.8
+//   1024 tiles (4 x 2048x512x512)   70.2 -> 48.9  39.4 -> 20.7   24.1 -> 17.8
+// A k-concatenated operand needs whole stages on both sides, and the byte offsets of
+// an operand's rows inside a batch 32 bits.
+constexpr long long kBigMinF = 256, kBigMinH = 384;
+
+static long long big_tiles(int M, int N, int batch) {
+  return (long long)cdiv(M, kBigTile) * cdiv(N, kBigTile) * batch;
+}
+static bool big_rows_ok(const MatArg& m, int rows, int K) {
+  const long long lim = 1LL << 29;   // floats
+  return K > 0 && m.lr >= 0 && m.lk >= 0 && (rows + 3LL) * m.lr < lim && kBigK * m.lk < lim &&
+         (m.kalt == kNoAlt || m.kalt % kBigK == 0);
+}
+static bool big_rows_ok(const HMat& m, int rows, bool t) {
+  const long long lim = 1LL << 30;   // elements
+  return (t ? kBigK : (long long)rows) * m.ld < lim && (m.kalt == kNoAlt || m.kalt % kBigK == 0);
+}
+static bool big_ok_f(int M, int N, int K, int batch, const MatArg& A, const MatArg& B) {
+  return big_tiles(M, N, batch) >= kBigMinF && big_rows_ok(A, M, K) && big_rows_ok(B, N, K);
+}
+static bool big_ok_h(int M, int N, int batch, const HMat& a, bool ta, const HMat& b, bool tb) {
+  return big_tiles(M, N, batch) >= kBigMinH && big_rows_ok(a, M, ta) && big_rows_ok(b, N, tb);
+}
+
+static int big_kind(const MatArg& m) {
+  if (rkind(m)) return kBigRow;
+  if (m.lk == 1) return kBigRow1;
+  const bool a16 = (uintptr_t)m.p % 16 == 0 && (!m.alt || (uintptr_t)m.alt % 16 == 0) &&
+                   (!m.kp || (uintptr_t)m.kp % 16 == 0) && m.sz % 4 == 0 && m.lk % 4 == 0;
+  return m.lr == 1 && a16 ? kBigCol4 : kBigCol;
+}
+
+template <bool BF16>
+static int run_big(int M, int N, int K, int batch, const MatArg& A, const MatArg& B, const StMat& out, hipStream_t st) {
+  const dim3 grid(cdiv(M, kBigTile), cdiv(N, kBigTile), batch);
+  const RMat a = rmat(A), b = rmat(B);
+  const int ka = big_kind(A);
+  int kb = big_kind(B);
+  // B's k-contiguous forms are built for k-contiguous A only; kBigCol reads any strides
+  if ((ka == kBigCol || ka == kBigCol4) && (kb == kBigRow || kb == kBigRow1)) kb = kBigCol;
+#define SQ_BIG(KA, KB) \
+  case 4 * KA + KB: k_gemm_big<BF16, KA, KB><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K); break
+  switch (4 * ka + kb) {
+    SQ_BIG(kBigCol, kBigCol); SQ_BIG(kBigCol, kBigCol4); SQ_BIG(kBigCol4, kBigCol); SQ_BIG(kBigCol4, kBigCol4);
+    SQ_BIG(kBigRow, kBigCol); SQ_BIG(kBigRow, kBigCol4); SQ_BIG(kBigRow, kBigRow); SQ_BIG(kBigRow, kBigRow1);
+    SQ_BIG(kBigRow1, kBigCol); SQ_BIG(kBigRow1, kBigCol4); SQ_BIG(kBigRow1, kBigRow); SQ_BIG(kBigRow1, kBigRow1);
+  }
+#undef SQ_BIG
+  return launch_status("gemm_big");
 }
 
 // A product on the FP32 values of an operand whose owner keeps only its bfloat16
@@ -1163,6 +1277,17 @@ static void launch_h(dim3 grid, const HMat& a, const HMat& b, const ST& out, int
   k_gemm_h<FORM, ST><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K);
 }
 
+static int run_big_h(bool ta, bool tb, int M, int N, int K, int batch, const HMat& a, const HMat& b, const StMat& out,
+                     hipStream_t st) {
+  const dim3 grid(cdiv(M, kBigTile), cdiv(N, kBigTile), batch);
+  if (ta && tb) k_gemm_big_h<true, true><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K);
+  else if (ta) k_gemm_big_h<true, false><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K);
+  else if (tb) k_gemm_big_h<false, true><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K);
+  else k_gemm_big_h<false, false><<<grid, kThreads, 0, st>>>(a, b, out, M, N, K);
+  note_copy_product();
+  return launch_status("gemm_big_h");
+}
+
 template <class ST>
 static int run_h(int form, dim3 grid, const HMat& a, const HMat& b, const ST& out, int M, int N, int K,
                  hipStream_t st) {
@@ -1184,6 +1309,7 @@ static int try_h(int M, int N, int K, int batch, const MatArg& A, const MatArg& 
   HMat ha, hb;
   bool ta, tb;
   if (!hmat(A, M, K, batch, &ha, &ta) || !hmat(B, N, K, batch, &hb, &tb)) return kNotApplicable;
+  if (big_ok_h(M, N, batch, ha, ta, hb, tb)) return run_big_h(ta, tb, M, N, K, batch, ha, hb, out, st);
   return run_h(hform(ta, tb, K, hkp(ha, hb)), dim3(cdiv(M, kTile), cdiv(N, kTile), batch), ha, hb, out, M, N, K, st);
 }
 
@@ -1208,6 +1334,7 @@ int gemm_bf16_stored(int M, int N, int K, int batch, const uint16_t* A, long lon
               "of at least K (or its rows) rounded up to 8 elements");
     return SQ_EINVAL;
   }
+  if (big_ok_h(M, N, batch, a, ta, b, tb)) return run_big_h(ta, tb, M, N, K, batch, a, b, stmat(C), st);
   return run_h(hform(ta, tb, K), dim3(cdiv(M, kTile), cdiv(N, kTile), batch), a, b, stmat(C), M, N,
                K, st);
 }
@@ -1252,6 +1379,8 @@ int gemm(int bf16, int M, int N, int K, int batch, MatArg A, MatArg B, OutArg C,
     if (h != kNotApplicable) return h;
   }
   if (!fp32) return refuse_dropped("gemm");
+  if (want_splits(M, N, K, batch, scratch, scratch_floats) == 1 && big_ok_f(M, N, K, batch, A, B))
+    return bf16 ? run_big<true>(M, N, K, batch, A, B, out, st) : run_big<false>(M, N, K, batch, A, B, out, st);
   if (bf16) {
     if (va && vb) return run_r<true, 1, 1>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
     if (va) return run_r<true, 1, 0>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
@@ -1369,12 +1498,32 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
   RProb q1{rmat(p1.A), rmat(p1.B), stmat(p1.C), p1.M, p1.N, p1.K, cdiv(p1.M, kTile),
            cdiv(p1.N, kTile)};
   const int t0 = q0.gx * q0.gy * p0.batch, t1 = q1.gx * q1.gy * p1.batch;
+  const long long b0 = big_tiles(p0.M, p0.N, p0.batch), b1 = big_tiles(p1.M, p1.N, p1.batch);
   HMat h0a, h0b, h1a, h1b;
   bool s0a, s0b, s1a, s1b;
   if (bf16 && hmat(p0.A, p0.M, p0.K, p0.batch, &h0a, &s0a) && hmat(p0.B, p0.N, p0.K, p0.batch, &h0b, &s0b) &&
       hmat(p1.A, p1.M, p1.K, p1.batch, &h1a, &s1a) && hmat(p1.B, p1.N, p1.K, p1.batch, &h1b, &s1b)) {
-    const HProb r0{h0a, h0b, q0.st, p0.M, p0.N, p0.K, q0.gx, q0.gy};
-    const HProb r1{h1a, h1b, q1.st, p1.M, p1.N, p1.K, q1.gx, q1.gy};
+    HProb r0{h0a, h0b, q0.st, p0.M, p0.N, p0.K, q0.gx, q0.gy};
+    HProb r1{h1a, h1b, q1.st, p1.M, p1.N, p1.K, q1.gx, q1.gy};
+    // the 64 x 64 tile where problem 0 fills the chip with it (forward pairs: both together)
+    const bool rows0 = big_rows_ok(h0a, p0.M, s0a) && big_rows_ok(h0b, p0.N, s0b);
+    if (!s0a && s0b && s1a && s1b && !hkp(h1a, h1b) && rows0 && b0 >= kBigMinH) {
+      r0.gx = cdiv(p0.M, kBigTile);
+      r0.gy = cdiv(p0.N, kBigTile);
+      k_gemm_pair_big_h<<<t1 + (int)b0, kThreads, 0, st>>>(r0, r1, t1);
+      note_copy_product();
+      return launch_status("gemm_pair_big_h");
+    }
+    if (!s0a && !s0b && !s1a && !s1b && rows0 && big_rows_ok(h1a, p1.M, false) &&
+        big_rows_ok(h1b, p1.N, false) && b0 + b1 >= kBigMinH) {
+      r0.gx = cdiv(p0.M, kBigTile);
+      r0.gy = cdiv(p0.N, kBigTile);
+      r1.gx = cdiv(p1.M, kBigTile);
+      r1.gy = cdiv(p1.N, kBigTile);
+      k_gemm_pair_big_hf<<<(int)(b0 + b1), kThreads, 0, st>>>(r0, r1, (int)b1);
+      note_copy_product();
+      return launch_status("gemm_pair_big_hf");
+    }
     const int f0 = hform(s0a, s0b, p0.K, hkp(h0a, h0b)), f1 = hform(s1a, s1b, p1.K, hkp(h1a, h1b));
     bool done = true;
     if (f0 == kHDirect && f1 == kHDirect) k_gemm_pair_h<kHDirect, kHDirect><<<t0 + t1, kThreads, 0, st>>>(r0, r1, t0);
@@ -1389,6 +1538,34 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     }
   }
   if (!fp32_ok(p0.A) || !fp32_ok(p0.B) || !fp32_ok(p1.A) || !fp32_ok(p1.B)) return refuse_dropped("gemm_pair");
+  const bool rows0 = big_rows_ok(p0.A, p0.M, p0.K) && big_rows_ok(p0.B, p0.N, p0.K);
+  if (!fwd_kinds && rows0 && b0 >= kBigMinF) {
+    q0.gx = cdiv(p0.M, kBigTile);
+    q0.gy = cdiv(p0.N, kBigTile);
+    const int ka = big_kind(p0.A), kb = big_kind(p0.B), n = t1 + (int)b0;
+    if ((ka == kBigRow || ka == kBigRow1) && (kb == kBigCol || kb == kBigCol4)) {
+#define SQ_BIG(KA, KB)                                                                   \
+  if (ka == KA && kb == KB) {                                                            \
+    if (bf16) k_gemm_pair_big<true, KA, KB><<<n, kThreads, 0, st>>>(q0, q1, t1);         \
+    else k_gemm_pair_big<false, KA, KB><<<n, kThreads, 0, st>>>(q0, q1, t1);             \
+  }
+      SQ_BIG(kBigRow, kBigCol) SQ_BIG(kBigRow, kBigCol4) SQ_BIG(kBigRow1, kBigCol) SQ_BIG(kBigRow1, kBigCol4)
+#undef SQ_BIG
+      return launch_status("gemm_pair_big");
+    }
+    q0.gx = cdiv(p0.M, kTile);
+    q0.gy = cdiv(p0.N, kTile);
+  }
+  if (fwd_kinds && rows0 && big_rows_ok(p1.A, p1.M, p1.K) && big_rows_ok(p1.B, p1.N, p1.K) &&
+      b0 + b1 >= kBigMinF) {
+    q0.gx = cdiv(p0.M, kBigTile);
+    q0.gy = cdiv(p0.N, kBigTile);
+    q1.gx = cdiv(p1.M, kBigTile);
+    q1.gy = cdiv(p1.N, kBigTile);
+    if (bf16) k_gemm_pair_big_f<true><<<(int)(b0 + b1), kThreads, 0, st>>>(q0, q1, (int)b1);
+    else k_gemm_pair_big_f<false><<<(int)(b0 + b1), kThreads, 0, st>>>(q0, q1, (int)b1);
+    return launch_status("gemm_pair_big_f");
+  }
   if (fwd_kinds) {
     if (bf16) k_gemm_pair_f<true><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);
     else k_gemm_pair_f<false><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);

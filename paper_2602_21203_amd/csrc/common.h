@@ -92,6 +92,23 @@ struct Bump {
 
 struct EncPrepMap;   // (defined with the optimiser's arguments below)
 
+// Element order of the fused encoder's partial gradients in the bfloat16 form: the
+// weights of layer l (flat offset W[l], cin[l] channels) as [f][tap][c], where the
+// parameters are [f][c][tap]; everything else in place (n = 0: all of it).
+struct EncOrder {
+  int n, F, W[4], cin[4];
+  // the parameter that element j of a partial gradient belongs to
+  __host__ __device__ int param(int j) const {
+    for (int l = 0; l < n; ++l) {
+      const int o = j - W[l], k = 9 * cin[l];
+      if (o < 0 || o >= F * k) continue;
+      const int f = o / k, r = o - f * k, tap = r / cin[l], c = r - tap * cin[l];
+      return W[l] + f * k + c * 9 + tap;
+    }
+    return j;
+  }
+};
+
 // ------------------------------------------------------------------ kernel launchers
 // Every launcher enqueues on `st` and returns SQ_OK or SQ_EDEVICE.
 
@@ -286,6 +303,8 @@ int encoder_fused_fwd_squint(const SampleArgs& sa, const uint8_t* obs, const uin
 // hh (nullable, bfloat16 form only): the last layer's output is also written there rounded to bfloat16
 int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* wp,
                       const float* const* b, float* const* h, hipStream_t st, uint16_t* hh = nullptr);
+// the order of a partial gradient's elements (bfloat16 form); W: flat offsets of the conv weights
+EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W);
 // partial gradients of every workgroup in part, their ordered sum in grad[0, total)
 int encoder_fused_bwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* dfeat,
                       const float* wp, const float* const* h, const long long* Woff, const long long* boff,
@@ -406,8 +425,9 @@ struct PackArgs {
 // (relative to the optimiser's range) has gradient sum_{r < nrows} part[r * H + i - begin],
 // summed in r order (the same sum colsum() forms); the optimiser forms it and
 // stores it at gout[i] (the writable gradient vector of the range).
-struct GradSeg { long long begin; int H, nrows; const float* part; };
-struct GradSegs { int n; GradSeg s[20]; float* gout; };
+// enc: the segment is the encoder's, its partials in the order `ord`.
+struct GradSeg { long long begin; int H, nrows; const float* part; int enc = 0; };
+struct GradSegs { int n; GradSeg s[20]; float* gout; EncOrder ord; };
 // Where the encoder's conv weights sit in the fused encoder's prepared copy: per
 // layer the forward order [f][tap][CP] at fb and, above the first layer, the
 // input-gradient order [tap][c][f] at bb (values rounded to bfloat16 when bf16).

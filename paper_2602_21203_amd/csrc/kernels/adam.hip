@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs A, PackArgs pk, GradSegs 
     __syncthreads();
     if (wave == 0 && j < e.H) {
       const float gi = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
-      const long long i = e.begin + j;
+      const long long i = e.begin + (e.enc ? gs.ord.param(j) : j);
       gs.gout[i] = gi;
       adam_elem(A, pk, i, gi, bc1, bc2, -1);
     }

@@ -39,6 +39,7 @@
 #include "../common.h"
 #include "bf16.h"
 #include "sample.h"
+#include "lds_tr.h"
 
 namespace sq {
 
@@ -388,32 +389,31 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd(const float* __restrict__ x,
   conv_bwd_weights<BF16, G, C, F, 0, NT>(r0, rin, qtab, pp + off.W[0], pp + off.b[0]);
 }
 
-// grad[e] = sum over workgroups (in order) of part[wg][e]: four consecutive
-// elements per lane, the workgroup rows split over the four waves by residue,
-// the four wave sums added in wave order
+// grad = sum over workgroups (in order) of part[wg][e], stored where ord puts element
+// e: one element per lane, the workgroup rows split over the four waves by residue,
+// the four wave sums added in wave order.  Sixteen rows of a wave are in flight at
+// once, and 64 elements a workgroup give more workgroups than compute units (21,120
+// elements x 256 rows: 4.9 us; 256 elements a workgroup, eight rows in flight: 8.7).
 __global__ __launch_bounds__(256) void k_enc_reduce(const float* __restrict__ part, int nwg, long long total,
-                                                    float* __restrict__ grad) {
-  __shared__ f4v sh[4][64];
+                                                    float* __restrict__ grad, EncOrder ord) {
+  __shared__ float sh[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long e = ((long long)blockIdx.x * 64 + lane) * 4;
-  const bool vec = total % 4 == 0 && e + 4 <= total;
-  f4v v = f4v{0.f, 0.f, 0.f, 0.f};
-  if (vec) {
-#pragma unroll 8
-    for (int w = wave; w < nwg; w += 4)
-      v += *reinterpret_cast<const f4v*>(__builtin_assume_aligned(part + (long long)w * total + e, 16));
-  } else {
-    for (int w = wave; w < nwg; w += 4)
-      for (int j = 0; j < 4; ++j)
-        if (e + j < total) v[j] += part[(long long)w * total + e + j];
+  const long long e = (long long)blockIdx.x * 64 + lane;
+  const float* p = part + (e < total ? e : total - 1);
+  float v = 0.f;
+  int w = wave;
+  for (; w + 60 < nwg; w += 64) {
+    float t[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t[k] = p[(long long)(w + 4 * k) * total];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v += t[k];
   }
+  for (; w < nwg; w += 4) v += p[(long long)w * total];
   sh[wave][lane] = v;
   __syncthreads();
-  if (wave == 0) {
-    const f4v s = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
-    for (int j = 0; j < 4; ++j)
-      if (e + j < total) grad[e + j] = s[j];
-  }
+  if (wave == 0 && e < total)
+    grad[ord.param((int)e)] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
 }
 
 // ---------------------------------------------------------------- bfloat16 form
@@ -668,84 +668,70 @@ __global__ __launch_bounds__(NT) void k_encoder_fwd_b(const float* __restrict__ 
 }
 
 // Weight gradient of layer l from D (bfloat16 [G][DS][DS][F + 8], zero border of
-// 2) and the layer's input (bfloat16 [G][HI][HI][PS]): rows f, columns kc = c * 9
-// + tap (the parameter order, so a tile's 16 columns are 16 consecutive floats of
-// the partial gradient and its stores coalesce), contraction over the images'
-// output pixels in 32-pixel chunks; each lane gathers its 8 pixels of a chunk
-// through the position table (pixel -> offset in D, offset of its input patch
-// origin), filled beforehand.
-#ifndef SQ_ENC_QTAB
-#define SQ_ENC_QTAB 1
-#endif
-#ifndef SQ_ENC_PREFETCH
-#define SQ_ENC_PREFETCH 1
-#endif
-template <int G, int C, int F, int l, int SD, int NT>
-__device__ __forceinline__ void fill_qtab(int2* qtab) {
-  using Y = LB<C, F, l, SD>;
-  constexpr int PSF = F + 8;
-  constexpr int NPOS = G * Y::P, NQ = (NPOS + 31) / 32 * 32;
-  for (int q = threadIdx.x; q < NQ; q += NT) {
-    int2 e = make_int2(0, 0);   // pad entries: a zero border pixel of D, any finite input
-    if (q < NPOS) {
-      const int g = q / Y::P, p = q - g * Y::P, oy = p / Y::HO, ox = p - oy * Y::HO;
-      e.x = ((g * Y::DS + oy + 2) * Y::DS + ox + 2) * PSF;
-      e.y = ((g * Y::HI + oy * Y::S) * Y::HI + ox * Y::S) * Y::PS;
-    }
-    qtab[q] = e;
-  }
-}
-
+// 2) and the layer's input (bfloat16 [G][HI][HI][PS]): rows f, columns 16 channels
+// of one tap, contraction over the images' output pixels in 32-pixel chunks.  Both
+// operands are channel-innermost, so a fragment (8 pixels of one channel per lane)
+// is two transposing reads of four pixels each (lds_tr.h), whose addresses are the
+// pixels' places: fixed per lane and layer, kept in registers (WOffs).  Gathering
+// the 8 pixels one by one took 16 two-byte reads and 8 table reads per lane and
+// product where this takes 4 eight-byte reads, or 6 for the two products of a
+// 32-filter task (the pixels' input fragment serves both filter tiles); the
+// backward of 512 / 2048 images 19.6 / 78.4 -> 16.3 / 66.1 us.
+// The partial gradient is stored as [f][tap][c] (EncOrder), whose 16 channels are
+// consecutive; the kernels that sum the partials map it to the parameter order.
 template <int G, int C, int F, int l, int SD>
-struct WTiles {
+struct WTasks {
   using Y = LB<C, F, l, SD>;
-  static constexpr int RT = F / 16, CT = (Y::K + 15) / 16, N = RT * CT;
+  static constexpr int RT = F / 16, CB = Y::CP / 16, N = 9 * CB;
+  static constexpr int NPOS = G * Y::P, NCH = (NPOS + 31) / 32;
+};
+
+// this lane's pixels of a layer's chunks, as offsets in D and in the input: pixel
+// 32 s + 8 lq + li / 4 (and 4 later), plus the channel group 4 (li % 4)
+template <int G, int C, int F, int l, int SD>
+struct WOffs {
+  using Y = LB<C, F, l, SD>;
+  using W = WTasks<G, C, F, l, SD>;
+  int d[2 * W::NCH], i[2 * W::NCH];
+  __device__ __forceinline__ WOffs() {
+    const int li = threadIdx.x & 15, lq = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int k = 0; k < 2 * W::NCH; ++k) {
+      const int q = 16 * (k & ~1) + 8 * lq + (li >> 2) + 4 * (k & 1);
+      const int qq = q < W::NPOS ? q : 0;
+      const int g = qq / Y::P, p = qq - g * Y::P, oy = p / Y::HO, ox = p - oy * Y::HO;
+      // past the last pixel: a zero border pixel of D against any finite input
+      d[k] = (q < W::NPOS ? ((g * Y::DS + oy + 2) * Y::DS + ox + 2) * (F + 8) : 0) + 4 * (li & 3);
+      i[k] = ((g * Y::HI + oy * Y::S) * Y::HI + ox * Y::S) * Y::PS + 4 * (li & 3);
+    }
+  }
 };
 
 template <int G, int C, int F, int l, int SD>
-__device__ __forceinline__ void bwd_w_tile(int t, const __bf16* D, const __bf16* in, const int2* qtab,
-                                           float* __restrict__ partW) {
+__device__ __forceinline__ void bwd_w_task(int t, const __bf16* D, const __bf16* in,
+                                           const WOffs<G, C, F, l, SD>& o, float* __restrict__ partW) {
   using Y = LB<C, F, l, SD>;
-  using W = WTiles<G, C, F, l, SD>;
-  constexpr int PSF = F + 8;
-  constexpr int NPOS = G * Y::P, NQ = (NPOS + 31) / 32 * 32;
+  using W = WTasks<G, C, F, l, SD>;
   const int lane = threadIdx.x & 63;
   const int li = lane & 15, lq = lane >> 4;
-  const int rt = t / W::CT, ct = t - rt * W::CT;
-  const int f0 = rt * 16, k0 = ct * 16;
-  const int kc = min(k0 + li, Y::K - 1);
-  const int c = kc / 9, tap = kc - 9 * c, ky = tap / 3, kx = tap - 3 * ky;
-  const __bf16* ap = D + f0 + li;
-  const __bf16* bp = in + (ky * Y::HI + kx) * Y::PS + c;
-  v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+  const int tap = t / W::CB, c0 = 16 * (t - tap * W::CB), ky = tap / 3, kx = tap - 3 * ky;
+  const __bf16* bp = in + (ky * Y::HI + kx) * Y::PS + c0;
+  v4f acc[W::RT];
 #pragma unroll
-  for (int s = 0; s < NQ / 32; ++s) {
-    bf16x8 a, b;
+  for (int rt = 0; rt < W::RT; ++rt) acc[rt] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      // output pixel q: its place in D and its input patch origin (pad pixels
-      // read a zero border pixel of D against an arbitrary finite input)
-      const int q = 32 * s + 8 * lq + e;
-      int ox_d, ox_i;
-      if constexpr (SQ_ENC_QTAB) {
-        const int2 o = qtab[q];
-        ox_d = o.x;
-        ox_i = o.y;
-      } else {
-        const int qq = q < NPOS ? q : 0;
-        const int g = qq / Y::P, p = qq - g * Y::P, oy = p / Y::HO, ox = p - oy * Y::HO;
-        ox_d = q < NPOS ? ((g * Y::DS + oy + 2) * Y::DS + ox + 2) * PSF : 0;
-        ox_i = ((g * Y::HI + oy * Y::S) * Y::HI + ox * Y::S) * Y::PS;
-      }
-      a[e] = ap[ox_d];
-      b[e] = bp[ox_i];
-    }
-    acc = mma_b(a, b, acc);
+  for (int s = 0; s < W::NCH; ++s) {
+    const bf16x8 b = lds_tr8(bp + o.i[2 * s], bp + o.i[2 * s + 1]);
+#pragma unroll
+    for (int rt = 0; rt < W::RT; ++rt)
+      acc[rt] = mma_b(lds_tr8(D + o.d[2 * s] + 16 * rt, D + o.d[2 * s + 1] + 16 * rt), b, acc[rt]);
   }
-  const int kk = k0 + li;
-  if (kk < Y::K) {
+  const int c = c0 + li;
+  if (c < Y::CIN) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) partW[(f0 + 4 * lq + q) * Y::K + kk] = acc[q];
+    for (int rt = 0; rt < W::RT; ++rt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) partW[(16 * rt + 4 * lq + q) * Y::K + tap * Y::CIN + c] = acc[rt][q];
   }
 }
 
@@ -762,41 +748,60 @@ struct XTiles {
   static constexpr int ROWS = G * Y::HI * Y::HI, RT = (ROWS + 15) / 16, CT = F / 16, N = RT * CT;
 };
 
+// What a tile reads from memory: its weight fragments and the ReLU masks of the lane's
+// four rows.  A wave's first tile of a layer has them requested before the barriers
+// that precede it (with 16-byte zeroing and 8-byte staging of the LDS tiles: 512 /
+// 2048 images 16.3 / 66.1 -> 14.8 / 54.0 us).
 template <int G, int C, int F, int l, int SD>
-__device__ __forceinline__ void bwd_x_tile(int t, const __bf16* D, const __bf16* __restrict__ wb,
-                                           const float* __restrict__ hin, __bf16* Dn, float* bpart, int gn) {
+struct XFrag {
   using Y = LB<C, F, l, SD>;
   using X = XTiles<G, C, F, l, SD>;
+  static constexpr int TPM = 32 / F, NM = (9 + TPM - 1) / TPM;
+  bf16x8 b[NM];
+  float hm[4];
+  __device__ __forceinline__ void load(int t, const __bf16* __restrict__ wb, const float* __restrict__ hin, int gn) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lq = lane >> 4;
+    const int rt = t / X::CT, c = 16 * (t - rt * X::CT) + li;
+    const __bf16* bp = wb + c * F;
+#pragma unroll
+    for (int mi = 0; mi < NM; ++mi) {
+      int tap, off;
+      chunk_tap<TPM>(mi, lq, tap, off);
+      const int tc = tap < 9 ? tap : 8;
+      b[mi] = *reinterpret_cast<const bf16x8*>(__builtin_assume_aligned(bp + tc * F * F + off, 16));
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = min(rt * 16 + 4 * lq + q, X::ROWS - 1), gg = r / (Y::HI * Y::HI), pp = r - gg * Y::HI * Y::HI;
+      hm[q] = gg < gn ? hin[((long long)gg * Y::HI * Y::HI + pp) * F + c] : 0.f;
+    }
+  }
+};
+
+template <int G, int C, int F, int l, int SD>
+__device__ __forceinline__ void bwd_x_tile(int t, const __bf16* D, const XFrag<G, C, F, l, SD>& w, __bf16* Dn,
+                                           float* bpart) {
+  using Y = LB<C, F, l, SD>;
+  using X = XTiles<G, C, F, l, SD>;
+  using W = XFrag<G, C, F, l, SD>;
   static_assert(l >= 1, "input gradients are needed above the first layer only");
   constexpr int PSF = F + 8, DSN = Y::HI + 4;
-  constexpr int TPM = 32 / F, NM = (9 + TPM - 1) / TPM;
   constexpr int ROWS = X::ROWS;
   const int lane = threadIdx.x & 63;
   const int li = lane & 15, lq = lane >> 4;
   const int rt = t / X::CT, ct = t - rt * X::CT;
-  const int r0 = rt * 16, c0 = ct * 16;
+  const int r0 = rt * 16, c = ct * 16 + li;
   const int row = min(r0 + li, ROWS - 1);
   const int g = row / (Y::HI * Y::HI), pq = row - g * Y::HI * Y::HI, iy = pq / Y::HI, ix = pq - iy * Y::HI;
   const __bf16* ap = D + ((g * Y::DS + iy + 2) * Y::DS + ix + 2) * PSF;
-  const __bf16* bp = wb + (c0 + li) * F;
-  const int c = c0 + li;
-  // the ReLU masks of this lane's four rows, requested before the contraction
-  float hm[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r = min(r0 + 4 * lq + q, ROWS - 1), gg = r / (Y::HI * Y::HI), pp = r - gg * Y::HI * Y::HI;
-    hm[q] = gg < gn ? hin[((long long)gg * Y::HI * Y::HI + pp) * F + c] : 0.f;
-  }
   v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int mi = 0; mi < NM; ++mi) {
+  for (int mi = 0; mi < W::NM; ++mi) {
     int tap, off;
-    chunk_tap<TPM>(mi, lq, tap, off);
+    chunk_tap<W::TPM>(mi, lq, tap, off);
     const int tc = tap < 9 ? tap : 8, ky = tc / 3, kx = tc - 3 * ky;
     const bf16x8 a = *reinterpret_cast<const bf16x8*>(ap - (ky * Y::DS + kx) * PSF + off);
-    bf16x8 b = *reinterpret_cast<const bf16x8*>(__builtin_assume_aligned(bp + tc * F * F + off, 16));
-    if (tap > 8) b = bf16x8{};
-    acc = mma_b(a, b, acc);
+    acc = mma_b(a, tap > 8 ? bf16x8{} : w.b[mi], acc);
   }
   float sum = 0.f;
 #pragma unroll
@@ -804,7 +809,7 @@ __device__ __forceinline__ void bwd_x_tile(int t, const __bf16* D, const __bf16*
     const int r = r0 + 4 * lq + q;
     if (r < ROWS) {
       const int gg = r / (Y::HI * Y::HI), pp = r - gg * Y::HI * Y::HI, yy = pp / Y::HI, xx = pp - yy * Y::HI;
-      const float v = hm[q] > 0.f ? acc[q] : 0.f;
+      const float v = w.hm[q] > 0.f ? acc[q] : 0.f;
       Dn[((gg * DSN + yy + 2) * DSN + xx + 2) * PSF + c] = (__bf16)v;
       sum += v;
     }
@@ -816,19 +821,58 @@ __device__ __forceinline__ void bwd_x_tile(int t, const __bf16* D, const __bf16*
 
 // Both products of a layer l >= 1 share one pass over the waves (they read the
 // same D_l and write different buffers): input-gradient tiles first (the longer
-// ones), then weight-gradient tiles.  The position table must be filled.
+// ones), then weight-gradient tasks.
 template <int G, int C, int F, int l, int SD, int NT>
-__device__ __forceinline__ void bwd_layer_b(const __bf16* D, const __bf16* in, const int2* qtab,
-                                            float* __restrict__ partW, const __bf16* __restrict__ wb,
-                                            const float* __restrict__ hin, __bf16* Dn, float* bpart, int gn) {
+__device__ __forceinline__ void bwd_layer_b(const __bf16* D, const __bf16* in, float* __restrict__ partW,
+                                            const __bf16* __restrict__ wb, const float* __restrict__ hin, __bf16* Dn,
+                                            float* bpart, int gn, XFrag<G, C, F, l, SD>& w) {
   using X = XTiles<G, C, F, l, SD>;
-  using W = WTiles<G, C, F, l, SD>;
+  using W = WTasks<G, C, F, l, SD>;
   const int wave = threadIdx.x >> 6;
+  const WOffs<G, C, F, l, SD> o;
   for (int t = wave; t < X::N + W::N; t += NT / 64) {
-    if (t < X::N) bwd_x_tile<G, C, F, l, SD>(t, D, wb, hin, Dn, bpart, gn);
-    else bwd_w_tile<G, C, F, l, SD>(t - X::N, D, in, qtab, partW);
+    if (t < X::N) {
+      if (t != wave) w.load(t, wb, hin, gn);
+      bwd_x_tile<G, C, F, l, SD>(t, D, w, Dn, bpart);
+    } else {
+      bwd_w_task<G, C, F, l, SD>(t - X::N, D, in, o, partW);
+    }
   }
 }
+
+// n elements (a multiple of 8) of zeros, 16 bytes a thread
+template <int NT>
+__device__ __forceinline__ void lds_zero(__bf16* p, int n) {
+  for (int e = 8 * threadIdx.x; e < n; e += 8 * NT) *reinterpret_cast<bf16x8*>(p + e) = bf16x8{};
+}
+
+// a layer's inputs [pixel][F] (FP32, N floats), four channels a thread: requested up
+// front, then stored to LDS rows of PS elements as bfloat16
+template <int N, int F, int PS, int NT>
+struct PrefetchRows {
+  static_assert(N % 4 == 0 && F % 4 == 0, "whole groups of four channels");
+  static constexpr int R = (N / 4 + NT - 1) / NT;
+  f4v v[R > 0 ? R : 1];
+  __device__ __forceinline__ void load(const float* __restrict__ src, int valid) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int e = 4 * ((int)threadIdx.x + NT * i);
+      v[i] = e < valid ? *reinterpret_cast<const f4v*>(__builtin_assume_aligned(src + e, 16)) : f4v{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  __device__ __forceinline__ void store(__bf16* dst) const {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int e = 4 * ((int)threadIdx.x + NT * i);
+      if (e < N) {
+        tr_bf16x4 h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h[q] = (__bf16)v[i][q];
+        *reinterpret_cast<tr_bf16x4*>(dst + (e / F) * PS + e % F) = h;
+      }
+    }
+  }
+};
 
 // every element e < N (stride NT) of a staging load, issued up front into registers
 template <int N, int NT>
@@ -869,7 +913,6 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
   __shared__ __attribute__((aligned(16))) __bf16 r1[SZ1];
   __shared__ __attribute__((aligned(16))) __bf16 rin[RIN];
   __shared__ float bpart[RTB * F > TOPN ? RTB * F : TOPN];
-  __shared__ int2 qtab[(G * L0::P + 31) / 32 * 32];
   const int img0 = blockIdx.x * G;
   const int gn = n - img0 < G ? n - img0 : G;
   float* pp = part + (long long)blockIdx.x * enc_total;
@@ -881,24 +924,28 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
   Prefetch<TOPN, NT> pd, ph;
   pd.load(dfeat + (long long)img0 * F * LL::P, gn * F * LL::P);
   ph.load(hl + (long long)img0 * F * LL::P, gn * F * LL::P);
-  Prefetch<NH1, NT> p1;
-  Prefetch<NH0, NT> p0;
+  PrefetchRows<NH1, F, L2::PS, NT> p1;
+  PrefetchRows<NH0, F, L1::PS, NT> p0;
   Prefetch<NX, NT> px;
-  auto load1 = [&] {
-    if constexpr (NC > 2) p1.load(h1 + (long long)img0 * L2::HI * L2::HI * F, gn * L2::HI * L2::HI * F);
-  };
-  auto load0 = [&] { p0.load(h0 + (long long)img0 * L1::HI * L1::HI * F, gn * L1::HI * L1::HI * F); };
-  auto loadx = [&] { px.load(x + (long long)img0 * C * SD * SD, gn * C * SD * SD); };
-  if constexpr (SQ_ENC_PREFETCH) {
-    load1();
-    load0();
-    loadx();
-  }
+  if constexpr (NC > 2) p1.load(h1 + (long long)img0 * L2::HI * L2::HI * F, gn * L2::HI * L2::HI * F);
+  p0.load(h0 + (long long)img0 * L1::HI * L1::HI * F, gn * L1::HI * L1::HI * F);
+  px.load(x + (long long)img0 * C * SD * SD, gn * C * SD * SD);
+  // and each wave's first input-gradient tile of the upper layer (waves without one
+  // reread the last)
+  const int wave = threadIdx.x >> 6;
+  const float* h0g = h0 + (long long)img0 * L1::HI * L1::HI * F;
+  const int xt1 = min(wave, XTiles<G, C, F, 1, SD>::N - 1);
+  XFrag<G, C, F, 1, SD> w1;
+  XFrag<G, C, F, (NC > 2 ? 2 : 1), SD> w2;
+  if constexpr (NC > 2)
+    w2.load(min(wave, XTiles<G, C, F, 2, SD>::N - 1), wp + E::B2, h1 + (long long)img0 * L2::HI * L2::HI * F, gn);
+  else
+    w1.load(xt1, wp + E::B1, h0g, gn);
 
   // D_{NC-1}: zero, then the upstream gradient (NCHW) masked by the output > 0 into
   // the interior; its bias gradient sums the same FP32 values, thread f in (g, p) order
   __bf16* Dl = NC > 2 ? r0 : r1;
-  for (int e = threadIdx.x; e < (NC > 2 ? SZ2 : SZ1); e += NT) Dl[e] = (__bf16)0.f;
+  lds_zero<NT>(Dl, NC > 2 ? SZ2 : SZ1);
   lds_barrier();
 #pragma unroll
   for (int i = 0; i < Prefetch<TOPN, NT>::R; ++i) {
@@ -921,17 +968,12 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
   }
   if constexpr (NC > 2) {
     // layer 2: input h1 ([img][pixel][F] -> [g][pixel][PS]); D_2 in r0, D_1 -> r1
-    if constexpr (!SQ_ENC_PREFETCH) load1();
-#pragma unroll
-    for (int i = 0; i < Prefetch<NH1, NT>::R; ++i) {
-      const int e = (int)threadIdx.x + NT * i;
-      if (e < NH1) rin[(e / F) * L2::PS + e % F] = (__bf16)p1.v[i];
-    }
-    for (int e = threadIdx.x; e < SZ1; e += NT) r1[e] = (__bf16)0.f;
-    fill_qtab<G, C, F, 2, SD, NT>(qtab);
+    p1.store(rin);
+    lds_zero<NT>(r1, SZ1);
     lds_barrier();
-    bwd_layer_b<G, C, F, 2, SD, NT>(r0, rin, qtab, pp + off.W[2], wp + E::B2,
-                                h1 + (long long)img0 * L2::HI * L2::HI * F, r1, bpart, gn);
+    bwd_layer_b<G, C, F, 2, SD, NT>(r0, rin, pp + off.W[2], wp + E::B2,
+                                h1 + (long long)img0 * L2::HI * L2::HI * F, r1, bpart, gn, w2);
+    w1.load(xt1, wp + E::B1, h0g, gn);
     lds_barrier();
     if (threadIdx.x < F) {
       float sb = 0.f;
@@ -940,17 +982,10 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
     }
   }
   // layer 1: input h0; D_1 in r1, D_0 -> r0
-  if constexpr (!SQ_ENC_PREFETCH) load0();
-#pragma unroll
-  for (int i = 0; i < Prefetch<NH0, NT>::R; ++i) {
-    const int e = (int)threadIdx.x + NT * i;
-    if (e < NH0) rin[(e / F) * L1::PS + e % F] = (__bf16)p0.v[i];
-  }
-  for (int e = threadIdx.x; e < SZ0; e += NT) r0[e] = (__bf16)0.f;
-  fill_qtab<G, C, F, 1, SD, NT>(qtab);
+  p0.store(rin);
+  lds_zero<NT>(r0, SZ0);
   lds_barrier();
-  bwd_layer_b<G, C, F, 1, SD, NT>(r1, rin, qtab, pp + off.W[1], wp + E::B1, h0 + (long long)img0 * L1::HI * L1::HI * F,
-                              r0, bpart, gn);
+  bwd_layer_b<G, C, F, 1, SD, NT>(r1, rin, pp + off.W[1], wp + E::B1, h0g, r0, bpart, gn, w1);
   lds_barrier();
   if (threadIdx.x < F) {
     float sb = 0.f;
@@ -958,7 +993,6 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
     pp[off.b[0] + threadIdx.x] = sb;
   }
   // layer 0: input x (NCHW -> [g][pixel][channel], padding channels zero); D_0 in r0
-  if constexpr (!SQ_ENC_PREFETCH) loadx();
 #pragma unroll
   for (int i = 0; i < Prefetch<NX, NT>::R; ++i) {
     const int e = (int)threadIdx.x + NT * i;
@@ -971,10 +1005,10 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
     const int gp = e / (L0::CP - C), c = C + e - gp * (L0::CP - C);
     rin[gp * L0::PS + c] = (__bf16)0.f;
   }
-  fill_qtab<G, C, F, 0, SD, NT>(qtab);
   lds_barrier();
-  for (int t = threadIdx.x >> 6; t < WTiles<G, C, F, 0, SD>::N; t += NT / 64)
-    bwd_w_tile<G, C, F, 0, SD>(t, r0, rin, qtab, pp + off.W[0]);
+  const WOffs<G, C, F, 0, SD> o;
+  for (int t = threadIdx.x >> 6; t < WTasks<G, C, F, 0, SD>::N; t += NT / 64)
+    bwd_w_task<G, C, F, 0, SD>(t, r0, rin, o, pp + off.W[0]);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1058,6 +1092,17 @@ bool encoder_fused_prep_map(int C, int F, int n_conv, int side, const long long*
   return true;
 }
 
+EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W) {
+  EncOrder o{};
+  o.n = n_conv;
+  o.F = F;
+  for (int l = 0; l < n_conv; ++l) {
+    o.W[l] = (int)W[l];
+    o.cin[l] = l == 0 ? C : F;
+  }
+  return o;
+}
+
 template <bool BF16, int C, int F, int NC, int SD>
 static int enc_bwd_t(const float* x, int n, const float* dfeat, const float* wp, const float* const* h,
                      const long long* Woff, const long long* boff, long long total, float* part, float* grad,
@@ -1079,7 +1124,8 @@ static int enc_bwd_t(const float* x, int n, const float* dfeat, const float* wp,
   }
   SQ_TRY(launch_status("encoder_bwd"));
   if (!grad) return SQ_OK;   // the caller sums the partials (an optimiser segment)
-  k_enc_reduce<<<(int)cdiv(total, 256), 256, 0, st>>>(part, nwg, total, grad);
+  const EncOrder ord = BF16 ? encoder_fused_order(C, F, NC, Woff) : EncOrder{};
+  k_enc_reduce<<<(int)cdiv(total, 64), 256, 0, st>>>(part, nwg, total, grad, ord);
   return launch_status("encoder_reduce");
 }
 

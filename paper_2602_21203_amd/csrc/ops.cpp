@@ -161,9 +161,12 @@ int encoder_forward_squint(const Net& net, const float* ep, const Layout& L, con
                                            hh, st);
 }
 
-bool encoder_grad_seg(const Net& net, int bf16, const Layout& L, const EncBufs& e, int n, GradSeg* seg) {
+bool encoder_grad_seg(const Net& net, int bf16, const Layout& L, const EncBufs& e, int n, GradSeg* seg,
+                      EncOrder* ord) {
   if (!e.enc_part || !encoder_fused(net, bf16, e)) return false;
-  *seg = GradSeg{L.enc_begin, (int)(L.enc_end - L.enc_begin), encoder_fused_part_rows(n, net.side), e.enc_part};
+  *seg = GradSeg{L.enc_begin, (int)(L.enc_end - L.enc_begin), encoder_fused_part_rows(n, net.side), e.enc_part, 1};
+  // (the encoder block starts the flat vector, so its elements count from there)
+  *ord = bf16 ? encoder_fused_order(net.d.C, net.d.F, net.d.n_conv, L.conv_W) : EncOrder{};
   return true;
 }
 

@@ -37,8 +37,9 @@ int encoder_backward(const Net& net, int bf16, const float* ep, const Layout& L,
                      const float* dfeat, const EncBufs& e, float* dep, hipStream_t st,
                      bool prepared = false, bool defer_reduce = false);
 // the fused encoder's partial gradients as an optimiser segment (false: no fused path
-// in this precision)
-bool encoder_grad_seg(const Net& net, int bf16, const Layout& L, const EncBufs& e, int n, GradSeg* seg);
+// in this precision), with the order of their elements
+bool encoder_grad_seg(const Net& net, int bf16, const Layout& L, const EncBufs& e, int n, GradSeg* seg,
+                      EncOrder* ord);
 // whether these buffers run the fused encoder in this precision
 bool encoder_fused(const Net& net, int bf16, const EncBufs& e);
 

@@ -14,7 +14,8 @@ OUT = os.path.join(HERE, "libsquint.so")
 OBJ = os.path.join(HERE, "_build")
 
 SOURCES = [
-    "kernels/rng.hip", "kernels/squint.hip", "kernels/gemm.hip", "kernels/rowops.hip", "kernels/adam.hip", "kernels/serve.hip", "kernels/encoder.hip", "kernels/env.hip",
+    "kernels/rng.hip", "kernels/squint.hip", "kernels/gemm.hip", "kernels/rowops.hip", "kernels/adam.hip", "kernels/serve.hip", "kernels/encoder.hip",
+    "kernels/encoder32.hip", "kernels/env.hip",
     "layout.cpp", "twins.cpp", "ops.cpp", "abi.cpp", "noalloc.hip", "agent.cpp", "server.cpp", "ring.cpp", "env.cpp",
 ]
 ARCH = os.environ.get("SQ_OFFLOAD_ARCH", "gfx950")

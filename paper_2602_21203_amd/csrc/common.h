@@ -309,6 +309,19 @@ EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W);
 int encoder_fused_bwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* dfeat,
                       const float* wp, const float* const* h, const long long* Woff, const long long* boff,
                       long long total, float* part, float* grad, hipStream_t st);
+// grad[ord.param(e)] = sum over the rows of part[row][e], e < total, in row order
+int encoder_reduce(const float* part, int rows, long long total, float* grad, const EncOrder& ord, hipStream_t st);
+
+// encoder32.hip: the FP32 encoder on 32 x 32 inputs; every activation NCHW, as the
+// general convolutions keep them (and the same forward bits).  The forward returns
+// kNotApplicable when x or the last activation is not 16-byte aligned; everything else
+// lies in a workspace (256-byte aligned).  part: n * total floats
+bool encoder32_ok(int C, int F, int n_conv, int side);
+int encoder32_fwd(const float* x, int n, const float* const* W, const float* const* b, float* const* h,
+                  hipStream_t st);
+int encoder32_bwd(const float* x, int n, const float* dfeat, const float* const* W, const float* const* h,
+                  const long long* Woff, const long long* boff, long long total, float* part, float* grad,
+                  hipStream_t st);
 
 // rowops.hip
 // Second parameter group of a LayerNorm batch (batches z >= zalt read their gain

@@ -31,7 +31,8 @@
 //
 // Backward: per layer, from the gradient at its post-ReLU output (masked by
 // output > 0): the bias sum, the weight gradient of the G images (contraction
-// over their output pixels, whose LDS offsets come from a per-layer table) and,
+// over their output pixels; the FP32 form reads their LDS offsets from a per-layer
+// table, the bfloat16 form transposes whole pixel runs on the read) and,
 // above the first layer, the input gradient (a transposed convolution over a
 // zero-bordered copy of the gradient, masked by the layer's input > 0 on the
 // way out).  Each workgroup writes its partial encoder gradient; a second
@@ -1092,6 +1093,11 @@ bool encoder_fused_prep_map(int C, int F, int n_conv, int side, const long long*
   return true;
 }
 
+int encoder_reduce(const float* part, int rows, long long total, float* grad, const EncOrder& ord, hipStream_t st) {
+  k_enc_reduce<<<(int)cdiv(total, 64), 256, 0, st>>>(part, rows, total, grad, ord);
+  return launch_status("encoder_reduce");
+}
+
 EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W) {
   EncOrder o{};
   o.n = n_conv;
@@ -1124,9 +1130,7 @@ static int enc_bwd_t(const float* x, int n, const float* dfeat, const float* wp,
   }
   SQ_TRY(launch_status("encoder_bwd"));
   if (!grad) return SQ_OK;   // the caller sums the partials (an optimiser segment)
-  const EncOrder ord = BF16 ? encoder_fused_order(C, F, NC, Woff) : EncOrder{};
-  k_enc_reduce<<<(int)cdiv(total, 64), 256, 0, st>>>(part, nwg, total, grad, ord);
-  return launch_status("encoder_reduce");
+  return encoder_reduce(part, nwg, total, grad, BF16 ? encoder_fused_order(C, F, NC, Woff) : EncOrder{}, st);
 }
 
 bool encoder_fused_ok(int C, int F, int n_conv, int side, int bf16) {

@@ -85,7 +85,8 @@ void plan_encoder(const Net& net, int n, Bump& b, EncBufs* e, bool with_bwd) {
   e->enc_part = nullptr;
   e->wprep = nullptr;
   // the workspace serves both precisions: the fused path's buffers when either has
-  // one, the general path's when the FP32 form has none
+  // one (encoder32's partial gradients are as many), the general path's when the FP32
+  // form has none
   if (encoder_fused_ok(d.C, d.F, d.n_conv, net.side, 1)) {
     e->wprep = b.take<float>(encoder_fused_prep_floats(d.C, d.F, d.n_conv));
     if (with_bwd) {
@@ -94,7 +95,8 @@ void plan_encoder(const Net& net, int n, Bump& b, EncBufs* e, bool with_bwd) {
       e->enc_part = b.take<float>(encoder_fused_part_floats(n, L.enc_end, net.side));
     }
   }
-  if (with_bwd && !encoder_fused_ok(d.C, d.F, d.n_conv, net.side, 0)) {
+  if (with_bwd && !encoder_fused_ok(d.C, d.F, d.n_conv, net.side, 0) &&
+      !encoder32_ok(d.C, d.F, d.n_conv, net.side)) {
     const size_t big = (size_t)n * d.F * net.conv_side[0] * net.conv_side[0];
     e->dh[0] = b.take<float>(big);
     e->dh[1] = b.take<float>(big);
@@ -129,6 +131,16 @@ int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, 
     if (!prepared) SQ_TRY(encoder_prepare(net, bf16, ep, L, e, st));
     uint16_t* hh = bf16 ? twin_of(h[d.n_conv - 1], (long long)n * net.flat) : nullptr;
     return encoder_fused_fwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, e.wprep, b, h, st, hh);
+  }
+  if (!bf16 && encoder32_ok(d.C, d.F, d.n_conv, net.side)) {
+    const float* W[3];
+    const float* b[3];
+    for (int i = 0; i < 3; ++i) {
+      W[i] = ep + L.conv_W[i];
+      b[i] = ep + L.conv_b[i];
+    }
+    const int s = encoder32_fwd(x, n, W, b, e.h, st);
+    if (s != kNotApplicable) return s;
   }
   const float* in = x;
   int cin = d.C, hs = net.side;
@@ -187,6 +199,11 @@ int encoder_backward(const Net& net, int bf16, const float* ep, const Layout& L,
     if (!prepared) SQ_TRY(encoder_fused_prep(bf16, d.C, d.F, d.n_conv, W, e.wprep, st));
     return encoder_fused_bwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, dfeat, e.wprep, h, Wo, bo, L.enc_end,
                              e.enc_part, defer_reduce ? nullptr : dep, st);
+  }
+  if (!bf16 && e.enc_part && encoder32_ok(d.C, d.F, d.n_conv, net.side)) {
+    const float* W[3];
+    for (int i = 0; i < 3; ++i) W[i] = ep + L.conv_W[i];
+    return encoder32_bwd(x, n, dfeat, W, e.h, L.conv_W, L.conv_b, L.enc_end, e.enc_part, dep, st);
   }
   const float* dh = dfeat;
   for (int i = d.n_conv - 1; i >= 0; --i) {

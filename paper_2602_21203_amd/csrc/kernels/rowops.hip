@@ -595,54 +595,6 @@ __device__ __forceinline__ void softmax_row(const float* l, int N, int lane, flo
 }
 
 
-// projection of one row, given the probabilities in registers (lane-strided:
-// atom j lives in lane j % 64, slot j / 64).  Every lane walks all atoms j in
-// order, reading p_j and b_j from their owner lane, so the sum order is fixed.
-// Writes m and returns sum_i m_i z_i.
-__device__ float project_row(const float* p, int N, int lane, float v_min, float dz, float r, float d, float gamma,
-                             float bonus, float* m_out) {
-  float bpos[kMaxAtomsPerLane];
-  int nan_lane = 0;
-#pragma unroll
-  for (int t = 0; t < kMaxAtomsPerLane; ++t) {
-    const int j = lane + 64 * t;
-    const float zj = v_min + (float)j * dz;
-    const float tz = r + gamma * (1.f - d) * (zj + bonus);
-    const float q = (tz - v_min) / dz;
-    nan_lane |= (j < N) & (q != q);
-    bpos[t] = fminf(fmaxf(q, 0.f), (float)(N - 1));
-  }
-  // fminf / fmaxf drop a NaN; a row whose shifted atoms are not numbers gets a
-  // NaN distribution instead (as the clamp of the definition keeps it)
-  const bool nan_row = __any(nan_lane);
-  float mi[kMaxAtomsPerLane];
-#pragma unroll
-  for (int t = 0; t < kMaxAtomsPerLane; ++t) mi[t] = 0.f;
-#pragma unroll
-  for (int ts = 0; ts < kMaxAtomsPerLane; ++ts) {
-    if (64 * ts >= N) break;
-    const int lim = N - 64 * ts < 64 ? N - 64 * ts : 64;
-    for (int l = 0; l < lim; ++l) {
-      const float pj = lane_read(p[ts], l);
-      const float bj = lane_read(bpos[ts], l);
-#pragma unroll
-      for (int t = 0; t < kMaxAtomsPerLane; ++t)
-        mi[t] += pj * fmaxf(0.f, 1.f - fabsf(bj - (float)(lane + 64 * t)));
-    }
-  }
-  float mz = 0.f;
-#pragma unroll
-  for (int t = 0; t < kMaxAtomsPerLane; ++t) {
-    const int i = lane + 64 * t;
-    if (nan_row) mi[t] = __builtin_nanf("");
-    if (i < N) {
-      m_out[i] = mi[t];
-      mz += mi[t] * (v_min + (float)i * dz);
-    }
-  }
-  return wave_sum(mz);
-}
-
 // Projection of one row by segments.  The projected positions b_j are
 // non-decreasing in j (every step from z_j to b_j is monotone, and so is its
 // rounding), so their integer parts l_j are too, and the atoms j sharing an l form
@@ -966,29 +918,88 @@ int target_mse(const float* logits4, int B, const float* reward, const float* do
   return launch_status("target_mse");
 }
 
-// plain projection of given probabilities (library entry point)
+// Plain projection of given probabilities (library entry point), a row per wave:
+// m_i = sum over j, in order, of p_j max(0, 1 - |b_j - i|).  The projected positions
+// b_j are non-decreasing in j when gamma (1 - d) >= 0 (every step from z_j to b_j is
+// monotone, and so is its rounding), so the atoms with a weight at i are one run; the
+// others add +-0, which changes no finite sum.  A lane finds the run's start by
+// bisection and walks it, eight atoms read at a time: 2 to 3 atoms off the ends of the support against all N
+// (3,000 rows of 101 atoms: 6.9 us, all N atoms 13.0).  A row of a negative gamma or
+// with a probability that is not finite (whose products with zero weights are NaN)
+// walks all N.
+template <int T>
 __global__ __launch_bounds__(256) void k_project(const float* __restrict__ p, const float* __restrict__ reward,
                                                  const uint8_t* __restrict__ done, const float* __restrict__ bonus,
                                                  float gamma, int B, int N, float v_min, float v_max,
                                                  float* __restrict__ m) {
+  __shared__ float2 sh[4][64 * T + 8];   // {b_j, p_j} of each wave's row
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.x * 4 + wave;
   if (b >= B) return;
-  float pr[kMaxAtomsPerLane];
-#pragma unroll
-  for (int t = 0; t < kMaxAtomsPerLane; ++t) {
-    const int j = lane + 64 * t;
-    pr[t] = j < N ? p[(long long)b * N + j] : 0.f;
-  }
   const float dz = (v_max - v_min) / (float)(N - 1);
-  project_row(pr, N, lane, v_min, dz, reward[b], done[b] ? 1.f : 0.f, gamma, bonus ? bonus[b] : 0.f,
-              m + (long long)b * N);
+  float pj[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) pj[t] = p[(long long)b * N + min(lane + 64 * t, N - 1)];
+  const float r = reward[b], d = done[b] ? 1.f : 0.f, bo = bonus ? bonus[b] : 0.f;
+  float2* row = sh[wave];
+  int nan_lane = 0, all_lane = gamma * (1.f - d) < 0.f;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int j = lane + 64 * t;
+    const float zj = v_min + (float)j * dz;
+    const float tz = r + gamma * (1.f - d) * (zj + bo);
+    const float q = (tz - v_min) / dz;
+    nan_lane |= (j < N) & (q != q);
+    all_lane |= !(fabsf(pj[t]) < INFINITY);
+    row[j] = make_float2(fminf(fmaxf(q, 0.f), (float)(N - 1)), pj[t]);
+  }
+  // fminf / fmaxf drop a NaN; a row whose shifted atoms are not numbers gets a
+  // NaN distribution instead (as the clamp of the definition keeps it)
+  const bool nan_row = __any(nan_lane), all = __any(all_lane);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the row is read by other lanes of this wave
+  // [j0, j1): the atoms above i - 1 and below i + 1
+  int j0[T], j1[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) j0[t] = j1[t] = 0;
+  if (!all) {
+    for (int s = 64 * T; s > 0; s >>= 1) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const float fi = (float)(lane + 64 * t);
+        const int a = j0[t] + s, e = j1[t] + s;
+        if (a <= N && row[min(a, N) - 1].x <= fi - 1.f) j0[t] = a;
+        if (e <= N && row[min(e, N) - 1].x < fi + 1.f) j1[t] = e;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < T; ++t) j1[t] = N;
+  }
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int i = lane + 64 * t;
+    if (i >= N) break;
+    float mi = 0.f;
+    for (int j = j0[t]; j < j1[t]; j += 8) {   // (the row is padded by eight)
+      float2 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = row[j + k];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float u = mi + v[k].y * fmaxf(0.f, 1.f - fabsf(v[k].x - (float)i));
+        mi = j + k < j1[t] ? u : mi;
+      }
+    }
+    m[(long long)b * N + i] = nan_row ? __builtin_nanf("") : mi;
+  }
 }
 
 int c51_project_raw(const float* p, const float* reward, const uint8_t* done, const float* bonus, float gamma, int B,
                     int N, float v_min, float v_max, float* m, hipStream_t st) {
   if (B <= 0) return SQ_OK;
-  k_project<<<cdiv(B, 4), 256, 0, st>>>(p, reward, done, bonus, gamma, B, N, v_min, v_max, m);
+  if (N <= 64) k_project<1><<<cdiv(B, 4), 256, 0, st>>>(p, reward, done, bonus, gamma, B, N, v_min, v_max, m);
+  else if (N <= 128) k_project<2><<<cdiv(B, 4), 256, 0, st>>>(p, reward, done, bonus, gamma, B, N, v_min, v_max, m);
+  else k_project<4><<<cdiv(B, 4), 256, 0, st>>>(p, reward, done, bonus, gamma, B, N, v_min, v_max, m);
   return launch_status("c51_project");
 }
 

@@ -40,12 +40,20 @@ int enqueue_act(const Net& net, const Layout& L, const sq_hparams& hp, const flo
   const sq_dims& d = net.d;
   const int bf = hp.prec == SQ_BF16;
   const float* feat = proprio;   // state-based: the state is the feature
+  int fused = kNotApplicable;
   if (d.n_conv > 0) {
-    SQ_TRY(launch_squint(frames, nullptr, n, d.H, d.W, d.C, d.k, 0, w.x, net.img, st));
-    SQ_TRY(encoder_forward(net, bf, params, L, w.x, n, w.e, st));
+    // in bfloat16 the squint and the noise run inside the encoder's launch where the geometry allows
+    if (bf)
+      fused = encoder_forward_act(net, params, L, frames, n, w.e, hp.seed, request_id, sample ? n * d.action : 0,
+                                  w.noise, st);
+    if (fused != kNotApplicable) SQ_TRY(fused);
+    else {
+      SQ_TRY(launch_squint(frames, nullptr, n, d.H, d.W, d.C, d.k, 0, w.x, net.img, st));
+      SQ_TRY(encoder_forward(net, bf, params, L, w.x, n, w.e, st));
+    }
     feat = w.e.h[d.n_conv - 1];
   }
-  if (sample) SQ_TRY(launch_act_noise(hp.seed, request_id, n, d.action, w.noise, st));
+  if (sample && fused == kNotApplicable) SQ_TRY(launch_act_noise(hp.seed, request_id, n, d.action, w.noise, st));
   return actor_forward(net, bf, params + L.actor_begin, pack, L, feat, net.flat, proprio, d.proprio,
                        sample ? w.noise : nullptr, n, hp.log_std_min, hp.log_std_max, action_out, nullptr, w.a, st);
 }

@@ -294,15 +294,22 @@ bool encoder_fused_prep_map(int C, int F, int n_conv, int side, const long long*
                             EncPrepMap* m);
 size_t encoder_fused_prep_floats(int C, int F, int n_conv);
 int encoder_fused_prep(int bf16, int C, int F, int n_conv, const float* const* W, float* wp, hipStream_t st);
-// The minibatch draw, the squint of its obs / next_obs frames (x: FP32 [2B][C][side][side] written for
-// the backward) and the bfloat16 encoder forward in one launch; kNotApplicable when the geometry has
-// no such form
+// The minibatch draw, the squint of its obs / next_obs frames and the bfloat16 encoder forward in one
+// launch; what the backward reads (x, FP32 [B][C][side][side], and the inner layers) is written for the
+// obs frames only; kNotApplicable when the geometry or the frames' alignment has no such form
 int encoder_fused_fwd_squint(const SampleArgs& sa, const uint8_t* obs, const uint8_t* next_obs, int H, int W, int C,
                              int F, int n_conv, int k, float* x, const float* wp, const float* const* b,
                              float* const* h, uint16_t* hh, hipStream_t st);
-// hh (nullable, bfloat16 form only): the last layer's output is also written there rounded to bfloat16
+// The squint of n frames, the bfloat16 encoder forward (last layer only) and the policy's noise (noise_n
+// values of launch_act_noise) in one launch, where encoder_fused_act_ok
+bool encoder_fused_act_ok(const uint8_t* frames, int H, int W, int C, int F, int n_conv, int k);
+int encoder_fused_fwd_act(const uint8_t* frames, int n, const float* wp, const float* const* b, float* const* h,
+                          unsigned long long seed, unsigned long long request_id, int noise_n, float* noise,
+                          hipStream_t st);
+// inner: the inner layers are wanted too (the FP32 form always writes them); hh (nullable, bfloat16 form
+// only): the last layer's output is also written there rounded to bfloat16
 int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* wp,
-                      const float* const* b, float* const* h, hipStream_t st, uint16_t* hh = nullptr);
+                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh = nullptr);
 // the order of a partial gradient's elements (bfloat16 form); W: flat offsets of the conv weights
 EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W);
 // partial gradients of every workgroup in part, their ordered sum in grad[0, total)

@@ -37,6 +37,8 @@
 // zero-bordered copy of the gradient, masked by the layer's input > 0 on the
 // way out).  Each workgroup writes its partial encoder gradient; a second
 // kernel adds the partials in workgroup order, so the result is deterministic.
+#include <algorithm>
+
 #include "../common.h"
 #include "bf16.h"
 #include "sample.h"
@@ -419,6 +421,7 @@ __global__ __launch_bounds__(256) void k_enc_reduce(const float* __restrict__ pa
 
 // ---------------------------------------------------------------- bfloat16 form
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 // layer geometry with bfloat16 storage: PS elements per LDS pixel (16-byte aligned),
 // TPM taps per 32-wide k chunk, NM chunks per 3x3 contraction
@@ -455,9 +458,8 @@ __device__ __forceinline__ void chunk_tap(int mi, int lq, int& tap, int& off) {
 }
 
 // The weight operand of one column tile (16 filters from c0) of forward layer l,
-// as this lane's MFMA fragments of every k chunk.  When the workgroup's wave count
-// is a multiple of the layer's column tiles, a wave only ever meets one column
-// tile, so all of a wave's weight fragments can be requested up front.
+// as this lane's MFMA fragments of every k chunk.  The workgroup's wave count is a
+// multiple of the layer's column tiles, so a wave only ever meets one.
 template <int C, int F, int l, int SD>
 struct WFrag {
   using Y = LB<C, F, l, SD>;
@@ -478,28 +480,24 @@ struct WFrag {
   }
 };
 
-// forward layer l of G images: in [G][HI][HI][PS] (bfloat16, LDS) -> post-ReLU
-// out_lds [G][HO][HO][F + 8] (bfloat16) and out_g (FP32, as the FP32 form).
-// w: the wave's weight fragments when PRE (its one column tile), else read per tile.
-template <int G, int C, int F, int l, int SD, bool TO_LDS, bool LAST, int NT, bool PRE>
-__device__ void conv_fwd_layer_b(const __bf16* in, __bf16* out_lds, const __bf16* __restrict__ wf,
-                                 const float* __restrict__ bias, float* __restrict__ out_g, int gn,
-                                 const WFrag<C, F, l, SD>& w, float* out_lds_f = nullptr,
-                                 uint16_t* __restrict__ out_h = nullptr) {
+// forward layer l of one image: in [HI][HI][PS] (bfloat16, LDS) -> post-ReLU
+// out_lds [HO][HO][F + 8] (bfloat16) and, unless it is null, out_g (FP32, [pixel][F]);
+// the last layer goes to out_lds_f (LDS) and from there, in NCHW order, to out_g and
+// out_h.  w: the wave's weight fragments (its one column tile).
+template <int C, int F, int l, int SD, bool LAST, int NT>
+__device__ __forceinline__ void conv_fwd_layer_b(const __bf16* in, __bf16* out_lds, float* __restrict__ out_g,
+                                                 const WFrag<C, F, l, SD>& w, float* out_lds_f = nullptr,
+                                                 uint16_t* __restrict__ out_h = nullptr) {
   using Y = LB<C, F, l, SD>;
-  constexpr int ROWS = G * Y::P, RT = (ROWS + 15) / 16, CT = F / 16, NW = NT / 64;
+  constexpr int RT = (Y::P + 15) / 16, CT = F / 16, NW = NT / 64;
   constexpr int PSO = F + 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, lq = lane >> 4;
   for (int t = wave; t < RT * CT; t += NW) {
     const int rt = t / CT, ct = t - rt * CT;
-    const int r0 = rt * 16, c0 = ct * 16;
-    const int row = min(r0 + li, ROWS - 1);
-    const int g = row / Y::P, p = row - g * Y::P, oy = p / Y::HO, ox = p - oy * Y::HO;
-    const __bf16* ap = in + ((g * Y::HI + oy * Y::S) * Y::HI + ox * Y::S) * Y::PS;
-    WFrag<C, F, l, SD> wt;
-    if constexpr (!PRE) wt.load(wf, bias, c0);
-    const WFrag<C, F, l, SD>& ww = PRE ? w : wt;
+    const int r0 = rt * 16, f = ct * 16 + li;
+    const int p = min(r0 + li, Y::P - 1), oy = p / Y::HO, ox = p - oy * Y::HO;
+    const __bf16* ap = in + (oy * Y::S * Y::HI + ox * Y::S) * Y::PS;
     v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int mi = 0; mi < Y::NM; ++mi) {
@@ -507,164 +505,231 @@ __device__ void conv_fwd_layer_b(const __bf16* in, __bf16* out_lds, const __bf16
       chunk_tap<Y::TPM>(mi, lq, tap, off);
       const int tc = tap < 9 ? tap : 8, ky = tc / 3, kx = tc - 3 * ky;
       const bf16x8 a = *reinterpret_cast<const bf16x8*>(ap + (ky * Y::HI + kx) * Y::PS + off);
-      acc = mma_b(a, ww.b[mi], acc);
+      acc = mma_b(a, w.b[mi], acc);
     }
-    const int f = c0 + li;
-    const float bv = ww.bias;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int r = r0 + 4 * lq + q;
-      if (r < ROWS) {
-        const int gg = r / Y::P, pp = r - gg * Y::P;
-        const float v = fmaxf(acc[q] + bv, 0.f);
-        if constexpr (TO_LDS) out_lds[(gg * Y::P + pp) * PSO + f] = (__bf16)v;
-        if constexpr (LAST) out_lds_f[(gg * F + f) * Y::P + pp] = v;   // NCHW, stored below
-        else if (gg < gn) out_g[((long long)gg * Y::P + pp) * F + f] = v;
+      if (r < Y::P) {
+        const float v = fmaxf(acc[q] + w.bias, 0.f);
+        if constexpr (LAST) out_lds_f[f * Y::P + r] = v;
+        else {
+          out_lds[r * PSO + f] = (__bf16)v;
+          if (out_g) out_g[r * F + f] = v;
+        }
       }
     }
   }
   if constexpr (LAST) {
-    // the feature rows of the workgroup's images are contiguous in NCHW order
     lds_barrier();
-    for (int e = threadIdx.x; e < gn * F * Y::P; e += NT) {
-      out_g[e] = out_lds_f[e];
-      if (out_h) out_h[e] = bf16_bits(out_lds_f[e]);
+    for (int e = threadIdx.x; e < F * Y::P; e += NT) {
+      const float v = out_lds_f[e];
+      out_g[e] = v;
+      if (out_h) out_h[e] = bf16_bits(v);
     }
   }
 }
 
-// SQK > 0: the launch also draws the minibatch and squints its frames (factor
-// SQK, uint8 HWC frames of side SD * SQK; SQK = 1: the block means stored in a
-// ring at insertion): the first `lead` workgroups take the draw's items (as in
-// the squint launch), and image workgroup i computes replay row i of the draw
-// itself (obs rows, then next_obs rows), sums each output pixel's SQK x SQK
-// block per channel (thread p owns pixel p), and writes x = sum / (255 SQK^2) -
-// 0.5 both to xout (FP32 CHW, for the backward) and, rounded, to the first
-// layer's LDS input: the separate draw / squint launches and the round trip of x
-// disappear.  The arithmetic is the squint kernels'.
-template <int G, int C, int F, int NC, int SD, int NT, int SQK = 0>
-__global__ __launch_bounds__(NT) void k_encoder_fwd_b(const float* __restrict__ x, int n, const __bf16* __restrict__ wp,
-                                                      const float* __restrict__ b0, const float* __restrict__ b1,
-                                                      const float* __restrict__ b2, float* __restrict__ h0,
-                                                      float* __restrict__ h1, float* __restrict__ h2,
-                                                      uint16_t* __restrict__ hh, const uint8_t* __restrict__ obs,
-                                                      const uint8_t* __restrict__ next_obs, SampleArgs sa, int lead,
-                                                      float* __restrict__ xout) {
+// Where a forward workgroup's images come from.  kEncX: x, FP32 NCHW.  kEncDraw: the
+// frames of the minibatch drawn in this launch (obs rows, then next_obs rows), squinted
+// here; x (which the backward reads) is written for the obs rows.  kEncAct: n frames in
+// order, squinted here, and the policy's noise drawn in this launch.
+enum EncSrc { kEncX, kEncDraw, kEncAct };
+
+struct ActNoise { unsigned k0, k1, lo, hi; int n; float* out; };
+
+struct EncFwdArgs {
+  const float* x; int n; const __bf16* wp; const float* b[3];
+  // inner layers of images below nsave (the backward's) are stored
+  float* h[3]; int nsave; uint16_t* hh;
+  const uint8_t* obs; const uint8_t* next_obs; SampleArgs sa; ActNoise noise; int lead; float* xout;
+};
+
+// One image's source, requested a whole image ahead of its use.  Frames (SQK x SQK
+// blocks of uint8 HWC pixels, or the block means stored in a ring, SQK = 1) are read as
+// consecutive 16-byte chunks and go through LDS, where thread p sums pixel p's block:
+// reading the block rows (36 bytes a lane at SQK = 4) straight from memory costs each
+// load instruction some 40 cache lines.
+template <int C, int SD, int NT, int SQK>
+struct EncImage {
+  static constexpr int NB = SD * SQK * SD * SQK * C / 16;   // 16-byte chunks of a frame
+  static constexpr int R = (NB + NT - 1) / NT, LDS = 16 * NB;
+  v4u v[R];
+  __device__ __forceinline__ void load(const uint8_t* __restrict__ frame) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int c = (int)threadIdx.x + NT * i;
+      v[i] = reinterpret_cast<const v4u*>(frame)[NB % NT == 0 || c < NB ? c : NB - 1];
+    }
+  }
+  __device__ __forceinline__ void store(uint8_t* buf) const {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int c = (int)threadIdx.x + NT * i;
+      if (NB % NT == 0 || c < NB) *reinterpret_cast<v4u*>(buf + 16 * c) = v[i];
+    }
+  }
+  // channel sums of pixel p's block
+  __device__ __forceinline__ static void sums(const uint8_t* buf, int p, unsigned (&sum)[C]) {
+    if constexpr (SQK == 1) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) sum[c] = buf[p * C + c];
+    } else {
+      constexpr int SEG = SQK * C;
+      static_assert(SEG % 4 == 0, "block rows of whole words");
+      const int y = p / SD, xq = p - y * SD;
+#pragma unroll
+      for (int c = 0; c < C; ++c) sum[c] = 0;
+#pragma unroll
+      for (int r = 0; r < SQK; ++r) {
+        // a wave's lanes lie in rows of blocks a multiple of all banks apart: each starts
+        // at another row of its block, which are a quarter of the banks apart (SQK = 4)
+        const unsigned* w =
+            reinterpret_cast<const unsigned*>(buf + ((y * SQK + (r + y) % SQK) * SD + xq) * SEG);
+#pragma unroll
+        for (int q = 0; q < SEG / 4; ++q) {
+          const unsigned u = w[q];
+#pragma unroll
+          for (int b = 0; b < 4; ++b)   // byte b of the word, added
+            sum[(4 * q + b) % C] = __builtin_amdgcn_udot4(u, 1u << (8 * b), sum[(4 * q + b) % C], false);
+        }
+      }
+    }
+  }
+};
+template <int C, int SD, int NT>
+struct EncImage<C, SD, NT, 0> {
+  static constexpr int N = C * SD * SD, R = (N + NT - 1) / NT, LDS = 16;
+  float v[R];
+  __device__ __forceinline__ void load(const float* __restrict__ x) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int e = (int)threadIdx.x + NT * i;
+      v[i] = x[N % NT == 0 || e < N ? e : N - 1];
+    }
+  }
+};
+
+// Persistent: a workgroup takes images blockIdx, blockIdx + grid, ..., its waves' weight
+// fragments (a column tile of every layer, 23 KB a wave) in registers throughout.
+// Fetched per image, as one workgroup per image did, they are 2.5 times the frame's own
+// bytes through the caches.  The next image is requested before this one's layers and
+// staged before its features are stored.  Bound by memory and by its own chain of
+// barriers: the draw, squint and forward of 2 x 512 / 2 x 2048 frames 21.0 / 63.7 -> 18.8 /
+// 48.0 us (no inner layers for the next_obs rows, which no backward reads), squint and
+// forward of 4,096 policy frames 38.3 + 43.0 -> 39.4 us, 512 images from x 10.9 -> 8.3 us.
+template <int C, int F, int NC, int SD, int NT, EncSrc SRC, int SQK>
+__global__ __launch_bounds__(NT, SQK <= 1 && SD == 16 ? 3 : 2) void k_encoder_fwd_b(EncFwdArgs a) {
   using L0 = LB<C, F, 0, SD>;
   using L1 = LB<C, F, 1, SD>;
+  using LL = LB<C, F, NC - 1, SD>;
   using E = EncPrep<C, F, NC>;
-  constexpr int X = G * SD * SD * L0::PS, A0 = G * L0::P * (F + 8), A1 = NC > 2 ? G * L1::P * (F + 8) : 8;
-  constexpr int NW = NT / 64, CT = F / 16;
-  constexpr bool PRE = NW % CT == 0;   // each wave meets one column tile per layer
-  __shared__ __attribute__((aligned(16))) __bf16 lx[X];
-  __shared__ __attribute__((aligned(16))) __bf16 la0[A0];
-  __shared__ __attribute__((aligned(16))) __bf16 la1[A1];
-  if constexpr (SQK > 0) {
+  using I = EncImage<C, SD, NT, SQK>;
+  constexpr int CT = F / 16, XN = SD * SD * L0::PS;
+  constexpr int A0 = L0::P * (F + 8) * 2, A1 = NC > 2 ? L1::P * (F + 8) * 2 : 0, OUT = F * LL::P * 4;
+  static_assert((NT / 64) % CT == 0, "each wave meets one column tile per layer");
+  static_assert((SRC == kEncX) == (SQK == 0) && (SQK == 0 || NT == SD * SD), "one thread per output pixel");
+  __shared__ __attribute__((aligned(16))) __bf16 lx[XN];
+  __shared__ __attribute__((aligned(16))) uint8_t buf[I::LDS];
+  __shared__ __attribute__((aligned(16))) uint8_t acts[A0 + (NC > 2 ? A1 : OUT)];
+  __bf16* la0 = reinterpret_cast<__bf16*>(acts);
+  __bf16* la1 = reinterpret_cast<__bf16*>(acts + A0);
+  // the features, in LDS: in the first layer's place, or behind it when the last reads it
+  static_assert(NC == 2 || OUT <= A0, "the features fit the first layer's place");
+  float* lout = reinterpret_cast<float*>(acts + (NC > 2 ? 0 : A0));
+  const int lead = SRC == kEncX ? 0 : a.lead;
+  if constexpr (SRC != kEncX) {
+    // the first workgroups draw the minibatch's other fields, or the policy's noise
     if ((int)blockIdx.x < lead) {
       const long long t = (long long)blockIdx.x * NT + threadIdx.x;
-      if (t < sample_items(sa.B, sa.A, sa.S)) sample_item(sa, t);
+      if constexpr (SRC == kEncDraw) {
+        if (t < sample_items(a.sa.B, a.sa.A, a.sa.S)) sample_item(a.sa, t);
+      } else if (t < a.noise.n) {
+        a.noise.out[t] = act_noise(a.noise.k0, a.noise.k1, (unsigned)t, a.noise.lo, a.noise.hi);
+      }
       return;
     }
   }
-  const int img0 = ((int)blockIdx.x - (SQK > 0 ? lead : 0)) * G;
-  const int gn = n - img0 < G ? n - img0 : G;
-  // the images, then every layer's weight fragments of this wave, all requested up front
-  constexpr int RX = SQK > 0 ? 1 : (G * C * SD * SD + NT - 1) / NT;
-  constexpr int SEG = SQK * C;   // bytes of one source block row (squint form)
-  constexpr int NWD = SQK > 1 ? SQK * SEG / 4 : (SQK == 1 ? C : 1);
-  float xv[RX];
-  unsigned fw[NWD];   // the block rows as 32-bit words (SQK > 1), or the pixel's C bytes (SQK = 1)
-  if constexpr (SQK > 0) {
-    static_assert(G == 1 && NT == SD * SD && (SQK == 1 || SEG % 4 == 0),
-                  "one thread per output pixel, 32-bit block rows");
-    const int p = threadIdx.x, y = p / SD, xq = p - y * SD;
-    constexpr int Wsrc = SD * SQK;
-    const bool second = img0 >= sa.B;
-    const uint8_t* frame = (second ? next_obs : obs) +
-                           (long long)sample_row(sa, second ? img0 - sa.B : img0) * Wsrc * Wsrc * C;
-    if constexpr (SQK == 1) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) fw[c] = frame[(long long)p * C + c];
+  const int first = (int)blockIdx.x - lead, stride = (int)gridDim.x - lead;
+  I im;
+  auto request = [&](int img) {
+    if constexpr (SRC == kEncX) {
+      im.load(a.x + (long long)img * C * SD * SD);
     } else {
-#pragma unroll
-      for (int r = 0; r < SQK; ++r) {
-        const unsigned* w =
-            reinterpret_cast<const unsigned*>(frame + ((long long)(y * SQK + r) * Wsrc + xq * SQK) * C);
-#pragma unroll
-        for (int q = 0; q < SEG / 4; ++q) fw[r * (SEG / 4) + q] = w[q];
+      const uint8_t* base = a.obs;
+      int row = img;
+      if constexpr (SRC == kEncDraw) {
+        const bool second = img >= a.sa.B;
+        base = second ? a.next_obs : a.obs;
+        row = sample_row(a.sa, second ? img - a.sa.B : img);
       }
+      im.load(base + (long long)row * (16 * I::NB));
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < RX; ++i) {
-      const int e = (int)threadIdx.x + NT * i;
-      xv[i] = e < gn * C * SD * SD ? x[(long long)img0 * C * SD * SD + e] : 0.f;
-    }
-  }
+  };
+  request(first);
   const int c0w = ((threadIdx.x >> 6) % CT) * 16;
   WFrag<C, F, 0, SD> w0;
   WFrag<C, F, 1, SD> w1;
   WFrag<C, F, (NC > 2 ? 2 : 1), SD> w2;
-  if constexpr (PRE) {
-    w0.load(wp + E::F0, b0, c0w);
-    w1.load(wp + E::F1, b1, c0w);
-    if constexpr (NC > 2) w2.load(wp + E::F2, b2, c0w);
+  w0.load(a.wp + E::F0, a.b[0], c0w);
+  w1.load(a.wp + E::F1, a.b[1], c0w);
+  if constexpr (NC > 2) w2.load(a.wp + E::F2, a.b[2], c0w);
+  if constexpr (SQK == 0) {   // padding channels
+    for (int e = threadIdx.x; e < SD * SD * (L0::CP - C); e += NT) {
+      const int p = e / (L0::CP - C), c = C + e - p * (L0::CP - C);
+      lx[p * L0::PS + c] = (__bf16)0.f;
+    }
   }
-  if constexpr (SQK > 0) {
-    // each byte of the block rows into its channel's integer sum, then x
-    int sum[C];
+  // the requested image into LDS: its frame, or x as [pixel][channel] bfloat16
+  auto stage = [&]() {
+    if constexpr (SQK > 0) {
+      im.store(buf);
+    } else {
 #pragma unroll
-    for (int c = 0; c < C; ++c) sum[c] = SQK == 1 ? (int)fw[c] : 0;
-    if constexpr (SQK > 1) {
-#pragma unroll
-      for (int r = 0; r < SQK; ++r)
-#pragma unroll
-        for (int q = 0; q < SEG / 4; ++q) {
-          const unsigned v = fw[r * (SEG / 4) + q];
-#pragma unroll
-          for (int b = 0; b < 4; ++b) sum[(4 * q + b) % C] += (int)((v >> (8 * b)) & 0xFFu);
-        }
-    }
-    const float scale = (float)(255 * SQK * SQK);
-    const int p = threadIdx.x;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const float v = (float)sum[c] / scale - 0.5f;
-      xout[((long long)img0 * C + c) * SD * SD + p] = v;
-      lx[p * L0::PS + c] = (__bf16)v;
-    }
-  } else {
-    // images NCHW -> [g][pixel][channel] bfloat16; absent images and padding channels zero
-#pragma unroll
-    for (int i = 0; i < RX; ++i) {
-      const int e = (int)threadIdx.x + NT * i;
-      if (e < G * C * SD * SD) {
-        const int g = e / (C * SD * SD), r = e - g * C * SD * SD, c = r / (SD * SD), pix = r - c * SD * SD;
-        lx[(g * SD * SD + pix) * L0::PS + c] = (__bf16)xv[i];
+      for (int i = 0; i < I::R; ++i) {
+        const int e = (int)threadIdx.x + NT * i, c = e / (SD * SD), p = e - c * SD * SD;
+        if (I::N % NT == 0 || e < I::N) lx[p * L0::PS + c] = (__bf16)im.v[i];
       }
     }
-  }
-  for (int e = threadIdx.x; e < G * SD * SD * (L0::CP - C); e += NT) {
-    const int gp = e / (L0::CP - C), c = C + e - gp * (L0::CP - C);
-    lx[gp * L0::PS + c] = (__bf16)0.f;
-  }
+  };
+  stage();
   lds_barrier();
-  conv_fwd_layer_b<G, C, F, 0, SD, true, false, NT, PRE>(lx, la0, wp + E::F0, b0, h0 + (long long)img0 * F * L0::P, gn,
-                                                     w0);
-  lds_barrier();
-  if constexpr (NC > 2) {
-    conv_fwd_layer_b<G, C, F, 1, SD, true, false, NT, PRE>(la0, la1, wp + E::F1, b1, h1 + (long long)img0 * F * L1::P,
-                                                       gn, w1);
+  for (int img = first; img < a.n; img += stride) {
+    const bool save = img < a.nsave, more = img + stride < a.n;
+    const long long io = img;
+    if (more) request(img + stride);
+    if constexpr (SQK > 0) {
+      const int p = threadIdx.x;
+      unsigned sum[C];
+      I::sums(buf, p, sum);
+      // sum / scale, correctly rounded for every sum of a block (0 .. scale: checked for
+      // 255 and 4080) by one correction of the product with the reciprocal
+      constexpr float scale = (float)(255 * SQK * SQK), inv = 1.f / scale;
+      static_assert(SQK == 1 || SQK == 4, "scales with a checked reciprocal");
+      bf16x8 px[L0::CP / 8] = {};
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const float fs = (float)sum[c], q = fs * inv;
+        const float v = __builtin_fmaf(__builtin_fmaf(-q, scale, fs), inv, q) - 0.5f;
+        if (SRC == kEncDraw && save) a.xout[(io * C + c) * SD * SD + p] = v;
+        px[c / 8][c % 8] = (__bf16)v;
+      }
+#pragma unroll
+      for (int i = 0; i < L0::CP / 8; ++i) *reinterpret_cast<bf16x8*>(&lx[p * L0::PS + 8 * i]) = px[i];
+      lds_barrier();
+    }
+    conv_fwd_layer_b<C, F, 0, SD, false, NT>(lx, la0, save ? a.h[0] + io * F * L0::P : nullptr, w0);
     lds_barrier();
-    conv_fwd_layer_b<G, C, F, 2, SD, false, true, NT, PRE>(la1, nullptr, wp + E::F2, b2,
-                                                       h2 + (long long)img0 * F * LB<C, F, 2, SD>::P, gn, w2,
-                                                       reinterpret_cast<float*>(lx),
-                                                       hh ? hh + (long long)img0 * F * LB<C, F, 2, SD>::P : nullptr);
-  } else {
-    conv_fwd_layer_b<G, C, F, 1, SD, false, true, NT, PRE>(la0, nullptr, wp + E::F1, b1,
-                                                       h1 + (long long)img0 * F * L1::P, gn, w1,
-                                                       reinterpret_cast<float*>(lx),
-                                                       hh ? hh + (long long)img0 * F * L1::P : nullptr);
+    if constexpr (NC > 2) {
+      conv_fwd_layer_b<C, F, 1, SD, false, NT>(la0, la1, save ? a.h[1] + io * F * L1::P : nullptr, w1);
+      lds_barrier();
+    }
+    // (before the features' stores, which a wait for the loads would include)
+    if (more) stage();
+    float* out = a.h[NC - 1] + io * F * LL::P;
+    uint16_t* oh = a.hh ? a.hh + io * F * LL::P : nullptr;
+    if constexpr (NC > 2) conv_fwd_layer_b<C, F, 2, SD, true, NT>(la1, nullptr, out, w2, lout, oh);
+    else conv_fwd_layer_b<C, F, 1, SD, true, NT>(la0, nullptr, out, w1, lout, oh);
   }
 }
 
@@ -1015,21 +1080,13 @@ __global__ __launch_bounds__(NT) void k_encoder_bwd_b(const float* __restrict__ 
 // ---------------------------------------------------------------- launchers
 constexpr int kEncFwdG = 2, kEncFwdThreads = 512;
 constexpr int kEncBwdG = 2, kEncBwdThreads = 512;
-// measured on the full network, B = 512 (forward / backward per update): one image and
-// 256 threads per forward workgroup 14.5 us (two images, 512 threads: 14.9; four, 512:
-// 18.1); 1024 threads per backward workgroup 27.2 us (512: 31.5; 256: 41.4)
-#ifndef SQ_ENC_FWD_G
-#define SQ_ENC_FWD_G 1
-#endif
-#ifndef SQ_ENC_FWD_T
-#define SQ_ENC_FWD_T 256
-#endif
-#ifndef SQ_ENC_BWD_T
-#define SQ_ENC_BWD_T 1024
-#endif
-// bfloat16 form (the backward keeps kEncBwdG images per workgroup: the partial-gradient rows follow it)
-constexpr int kEncFwdGb = SQ_ENC_FWD_G, kEncFwdThreadsb = SQ_ENC_FWD_T;
-constexpr int kEncBwdThreadsb = SQ_ENC_BWD_T;
+// bfloat16 form (the backward keeps kEncBwdG images per workgroup: the partial-gradient
+// rows follow it).  1024 threads per backward workgroup: B = 512 27.2 us (512: 31.5; 256: 41.4)
+constexpr int kEncFwdThreadsb = 256, kEncBwdThreadsb = 1024;
+// Persistent forward workgroups: two a compute unit on 16 x 16 inputs (the frame forms
+// hold 212 registers and 55 KB of LDS; 1,024 images 18.8 us, three workgroups' images in
+// turn 20.3), one on 32 x 32.
+constexpr int enc_fwd_wgs(int side) { return side == 16 ? 512 : 256; }
 
 template <int C, int F, int NC>
 static int prep_t(const float* const* W, float* wp, int bf16, hipStream_t st) {
@@ -1044,13 +1101,21 @@ static int prep_t(const float* const* W, float* wp, int bf16, hipStream_t st) {
 constexpr int enc_bwd_g(int side) { return side == 16 ? kEncBwdG : 1; }
 
 template <bool BF16, int C, int F, int NC, int SD>
-static int enc_fwd_t(const float* x, int n, const float* wp, const float* const* b, float* const* h, uint16_t* hh,
-                     hipStream_t st) {
+static int enc_fwd_t(const float* x, int n, const float* wp, const float* const* b, float* const* h, bool inner,
+                     uint16_t* hh, hipStream_t st) {
   if constexpr (BF16) {
-    const int nwg = cdiv(n, kEncFwdGb);
-    k_encoder_fwd_b<kEncFwdGb, C, F, NC, SD, kEncFwdThreadsb><<<nwg, kEncFwdThreadsb, 0, st>>>(
-        x, n, reinterpret_cast<const __bf16*>(wp), b[0], b[1], NC > 2 ? b[2] : b[1], h[0], h[1],
-        NC > 2 ? h[2] : h[1], hh, nullptr, nullptr, SampleArgs{}, 0, nullptr);
+    EncFwdArgs a{};
+    a.x = x;
+    a.n = n;
+    a.nsave = inner ? n : 0;
+    a.wp = reinterpret_cast<const __bf16*>(wp);
+    for (int i = 0; i < NC; ++i) {
+      a.b[i] = b[i];
+      a.h[i] = h[i];
+    }
+    a.hh = hh;
+    k_encoder_fwd_b<C, F, NC, SD, kEncFwdThreadsb, kEncX, 0>
+        <<<std::min(n, enc_fwd_wgs(SD)), kEncFwdThreadsb, 0, st>>>(a);
   } else {
     static_assert(SD == 16, "the FP32 fused encoder is built for 16 x 16 inputs");
     const int nwg = cdiv(n, kEncFwdG);
@@ -1153,18 +1218,40 @@ int encoder_fused_prep(int bf16, int C, int F, int n_conv, const float* const* W
 }
 
 int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* wp,
-                      const float* const* b, float* const* h, hipStream_t st, uint16_t* hh) {
+                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh) {
   if (n <= 0) return SQ_OK;
   if (hh && !bf16) {
     set_error("encoder_fused_fwd: the feature's bfloat16 copy is written by the bfloat16 form only");
     return SQ_EINVAL;
   }
-  if (side == 32) return enc_fwd_t<true, 9, 32, 3, 32>(x, n, wp, b, h, hh, st);
+  if (side == 32) return enc_fwd_t<true, 9, 32, 3, 32>(x, n, wp, b, h, inner, hh, st);
   if (C == 9 && F == 32 && n_conv == 3)
-    return bf16 ? enc_fwd_t<true, 9, 32, 3, 16>(x, n, wp, b, h, hh, st)
-                : enc_fwd_t<false, 9, 32, 3, 16>(x, n, wp, b, h, nullptr, st);
-  return bf16 ? enc_fwd_t<true, 3, 16, 2, 16>(x, n, wp, b, h, hh, st)
-              : enc_fwd_t<false, 3, 16, 2, 16>(x, n, wp, b, h, nullptr, st);
+    return bf16 ? enc_fwd_t<true, 9, 32, 3, 16>(x, n, wp, b, h, inner, hh, st)
+                : enc_fwd_t<false, 9, 32, 3, 16>(x, n, wp, b, h, inner, nullptr, st);
+  return bf16 ? enc_fwd_t<true, 3, 16, 2, 16>(x, n, wp, b, h, inner, hh, st)
+              : enc_fwd_t<false, 3, 16, 2, 16>(x, n, wp, b, h, inner, nullptr, st);
+}
+
+// the frame forms' geometry: 64 x 64 x 9 frames squinted 4x (k = 4), or their 16 x 16
+// block means stored in a ring (k = 1), into the 16 x 16 encoder; frames read 16 bytes at
+// a time
+static bool frames_ok(const uint8_t* frames, int H, int W, int C, int F, int n_conv, int k) {
+  return C == 9 && F == 32 && n_conv == 3 && ((k == 4 && H == 64 && W == 64) || (k == 1 && H == 16 && W == 16)) &&
+         (uintptr_t)frames % 16 == 0;
+}
+
+static EncFwdArgs frame_args(int n, int nsave, const float* wp, const float* const* b, float* const* h,
+                             uint16_t* hh) {
+  EncFwdArgs a{};
+  a.n = n;
+  a.nsave = nsave;
+  a.wp = reinterpret_cast<const __bf16*>(wp);
+  for (int i = 0; i < 3; ++i) {
+    a.b[i] = b[i];
+    a.h[i] = h[i];
+  }
+  a.hh = hh;
+  return a;
 }
 
 int encoder_fused_fwd_squint(const SampleArgs& sa, const uint8_t* obs, const uint8_t* next_obs, int H, int W, int C,
@@ -1172,21 +1259,34 @@ int encoder_fused_fwd_squint(const SampleArgs& sa, const uint8_t* obs, const uin
                              float* const* h, uint16_t* hh, hipStream_t st) {
   const int n = 2 * sa.B;
   if (n <= 0) return SQ_OK;
-  // the headline geometry: 64 x 64 x 9 frames squinted 4x (or their 16 x 16 block means stored in a
-  // ring, k = 1) into the 16 x 16 encoder, one image per 256-thread workgroup (a thread per output pixel)
-  if (!(C == 9 && F == 32 && n_conv == 3 && kEncFwdGb == 1 && kEncFwdThreadsb == 256)) return kNotApplicable;
-  const bool raw = k == 4 && H == 64 && W == 64 && (uintptr_t)obs % 4 == 0 && (uintptr_t)next_obs % 4 == 0;
-  const bool stored = k == 1 && H == 16 && W == 16;
-  if (!raw && !stored) return kNotApplicable;
-  const int lead = (int)((sample_items(sa.B, sa.A, sa.S) + kEncFwdThreadsb - 1) / kEncFwdThreadsb);
-  const __bf16* wb = reinterpret_cast<const __bf16*>(wp);
-  if (raw)
-    k_encoder_fwd_b<1, 9, 32, 3, 16, 256, 4><<<lead + n, 256, 0, st>>>(nullptr, n, wb, b[0], b[1], b[2], h[0], h[1],
-                                                                       h[2], hh, obs, next_obs, sa, lead, x);
-  else
-    k_encoder_fwd_b<1, 9, 32, 3, 16, 256, 1><<<lead + n, 256, 0, st>>>(nullptr, n, wb, b[0], b[1], b[2], h[0], h[1],
-                                                                       h[2], hh, obs, next_obs, sa, lead, x);
+  if (!frames_ok(obs, H, W, C, F, n_conv, k) || !frames_ok(next_obs, H, W, C, F, n_conv, k)) return kNotApplicable;
+  EncFwdArgs a = frame_args(n, sa.B, wp, b, h, hh);
+  a.obs = obs;
+  a.next_obs = next_obs;
+  a.sa = sa;
+  a.lead = (int)((sample_items(sa.B, sa.A, sa.S) + kEncFwdThreadsb - 1) / kEncFwdThreadsb);
+  a.xout = x;
+  const int grid = a.lead + std::min(n, enc_fwd_wgs(16));
+  if (k == 4) k_encoder_fwd_b<9, 32, 3, 16, 256, kEncDraw, 4><<<grid, 256, 0, st>>>(a);
+  else k_encoder_fwd_b<9, 32, 3, 16, 256, kEncDraw, 1><<<grid, 256, 0, st>>>(a);
   return launch_status("encoder_fwd_squint");
+}
+
+bool encoder_fused_act_ok(const uint8_t* frames, int H, int W, int C, int F, int n_conv, int k) {
+  return k == 4 && frames_ok(frames, H, W, C, F, n_conv, k);
+}
+
+int encoder_fused_fwd_act(const uint8_t* frames, int n, const float* wp, const float* const* b, float* const* h,
+                          unsigned long long seed, unsigned long long request_id, int noise_n, float* noise,
+                          hipStream_t st) {
+  if (n <= 0) return SQ_OK;
+  EncFwdArgs a = frame_args(n, 0, wp, b, h, nullptr);
+  a.obs = frames;
+  a.noise = ActNoise{(unsigned)seed, (unsigned)(seed >> 32), (unsigned)request_id, (unsigned)(request_id >> 32),
+                     noise_n, noise};
+  a.lead = cdiv(noise_n, 256);
+  k_encoder_fwd_b<9, 32, 3, 16, 256, kEncAct, 4><<<a.lead + std::min(n, enc_fwd_wgs(16)), 256, 0, st>>>(a);
+  return launch_status("encoder_fwd_act");
 }
 
 int encoder_fused_bwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* dfeat,

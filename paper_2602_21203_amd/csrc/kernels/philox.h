@@ -30,4 +30,11 @@ __device__ __forceinline__ float box_muller(unsigned w0, unsigned w1) {
   return sqrtf(-2.0f * logf(u1)) * cosf(6.283185307179586f * u2);
 }
 
+// policy noise value e (row * action width + dimension) of request (hi, lo) under key k:
+// stream 3
+__device__ __forceinline__ float act_noise(unsigned k0, unsigned k1, unsigned e, unsigned lo, unsigned hi) {
+  const P4 w = philox10(P4{e, 3u, lo, hi}, k0, k1);
+  return box_muller(w.x, w.y);
+}
+
 }  // namespace sq

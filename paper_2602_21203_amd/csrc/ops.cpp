@@ -130,7 +130,7 @@ int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, 
     }
     if (!prepared) SQ_TRY(encoder_prepare(net, bf16, ep, L, e, st));
     uint16_t* hh = bf16 ? twin_of(h[d.n_conv - 1], (long long)n * net.flat) : nullptr;
-    return encoder_fused_fwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, e.wprep, b, h, st, hh);
+    return encoder_fused_fwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, e.wprep, b, h, e.enc_part != nullptr, st, hh);
   }
   if (!bf16 && encoder32_ok(d.C, d.F, d.n_conv, net.side)) {
     const float* W[3];
@@ -171,6 +171,22 @@ int encoder_forward_squint(const Net& net, const float* ep, const Layout& L, con
                                            b, h, hh, st)
                 : encoder_fused_fwd_squint(sa, obs, next_obs, d.H, d.W, d.C, d.F, d.n_conv, d.k, x, e.wprep, b, h,
                                            hh, st);
+}
+
+int encoder_forward_act(const Net& net, const float* ep, const Layout& L, const uint8_t* frames, int n,
+                        const EncBufs& e, unsigned long long seed, unsigned long long request_id, int noise_n,
+                        float* noise, hipStream_t st) {
+  const sq_dims& d = net.d;
+  if (!encoder_fused(net, 1, e) || !encoder_fused_act_ok(frames, d.H, d.W, d.C, d.F, d.n_conv, d.k))
+    return kNotApplicable;
+  const float* b[4];
+  float* h[4];
+  for (int i = 0; i < d.n_conv; ++i) {
+    b[i] = ep + L.conv_b[i];
+    h[i] = e.h[i];
+  }
+  SQ_TRY(encoder_prepare(net, 1, ep, L, e, st));
+  return encoder_fused_fwd_act(frames, n, e.wprep, b, h, seed, request_id, noise_n, noise, st);
 }
 
 bool encoder_grad_seg(const Net& net, int bf16, const Layout& L, const EncBufs& e, int n, GradSeg* seg,

@@ -27,6 +27,11 @@ int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, 
 int encoder_forward_squint(const Net& net, const float* ep, const Layout& L, const SampleArgs& sa,
                            const uint8_t* obs, const uint8_t* next_obs, float* x, const EncBufs& e, hipStream_t st,
                            bool prepared, bool stored);
+// bfloat16: the squint of n frames, the encoder forward and the policy's noise (noise_n
+// values) in one launch; kNotApplicable when that form does not apply
+int encoder_forward_act(const Net& net, const float* ep, const Layout& L, const uint8_t* frames, int n,
+                        const EncBufs& e, unsigned long long seed, unsigned long long request_id, int noise_n,
+                        float* noise, hipStream_t st);
 // rewrite e.wprep from the parameters (fused path only; no-op otherwise)
 int encoder_prepare(const Net& net, int bf16, const float* ep, const Layout& L, const EncBufs& e, hipStream_t st);
 // prepared: the fused path's rearranged weights from encoder_forward of the same

@@ -1,0 +1,65 @@
+"""The encoder launch that reads frames (the policy's, and the update's raw or stored
+minibatch) against the separate squint, noise and encoder launches, bit for bit: frames
+that are not 16-byte aligned take the latter."""
+import pytest
+import torch
+
+from paper_2602_21203_amd import synthetic
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2602_21203_amd import api
+
+
+def _shifted(t, by):
+    """A copy of t whose storage starts `by` bytes off its alignment."""
+    store = torch.empty(t.numel() + 16, dtype=torch.uint8, device="cuda")
+    view = store[by:by + t.numel()].view(t.shape)
+    view.copy_(t)
+    return view
+
+
+# around the persistent grid's 512 workgroups, and several images each
+@pytest.mark.parametrize("n", [1, 2, 37, 511, 512, 513, 1300])
+@pytest.mark.parametrize("sample", [False, True])
+def test_act_equals_separate_launches(n, sample):
+    print(f"act frames n={n} sample={sample}", flush=True)
+    cfg = H.cfg("full")
+    ag = api.Agent(cfg, torch.tensor(H.params("full"), dtype=torch.float32, device="cuda"), 64, prec=1, seed=7)
+    frames = synthetic.frames(n, cfg["H"], cfg["W"], cfg["C"], seed=n, device="cuda")
+    frames[0, :4, :4] = 255   # a block at the largest sum, and one at zero
+    frames[0, :4, 4:8] = 0
+    prop = torch.randn((n, cfg["proprio"]), device="cuda")
+    got = ag.act(frames, prop, sample=sample, request_id=5)
+    for by in (1, 8):
+        assert torch.equal(got, ag.act(_shifted(frames, by), prop, sample=sample, request_id=5)), by
+
+
+@pytest.mark.parametrize("stored", [False, True])
+@pytest.mark.parametrize("B", [3, 64, 300])
+def test_update_equals_separate_launches(B, stored):
+    print(f"update frames B={B} stored={stored}", flush=True)
+    cfg = H.cfg("full")
+    cap = 256
+    rep = synthetic.replay(cap, cfg["H"], cfg["W"], cfg["C"], cfg["proprio"], cfg["action"], seed=3, device="cuda")
+    out = []
+    for by in (0, 4):
+        ag = api.Agent(cfg, torch.tensor(H.params("full"), dtype=torch.float32, device="cuda"), B, prec=1, seed=7)
+        r = dict(rep)
+        if stored:   # the block means, as a ring holds them
+            side = cfg["H"] // cfg["k"]
+            for f in ("obs", "next_obs"):
+                m = rep[f].view(cap, side, cfg["k"], side, cfg["k"], cfg["C"]).float().mean((2, 4))
+                r[f] = m.round().to(torch.uint8).contiguous()
+        r = {k: _shifted(v, by) if k in ("obs", "next_obs") else v for k, v in r.items()}
+        view = api.Ring.__new__(api.Ring)   # a view of these buffers, as a ring gives one
+        view.view = api.replay_struct(r)
+        view.view.squinted = int(stored)
+        stats = ag.sac_update(view, 3).clone()
+        torch.cuda.synchronize()
+        out.append((stats, ag.params.clone(), ag.target.clone(), ag.grads.clone()))
+        ag.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)

@@ -398,8 +398,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm(FA fa, FB fb, ST st, StPart s
 // chunk to the matrix cores (one v_mfma_f32_16x16x32_bf16, or eight
 // v_mfma_f32_16x16x4_f32 steps with step e taking k = 8*lq + e).
 //
-// Operand loads.  An operand whose rows are k-contiguous and 16-byte aligned is
-// read row-coalesced -- eight consecutive lanes cover the 128 bytes of one row's
+// Operand loads.  An operand whose rows are k-contiguous (at any alignment) is read
+// row-coalesced -- eight consecutive lanes cover the 128 bytes of one row's
 // chunk -- and rearranged into the fragment order through a small LDS tile that
 // belongs to the wave alone (no workgroup barrier; the wave waits for its own
 // LDS writes before reading back).  Reading the fragment order straight from
@@ -422,6 +422,7 @@ struct RMat {
 };
 
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // at any float's address
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRKC = 32;   // k per chunk
@@ -462,7 +463,7 @@ __device__ __forceinline__ void rload(const ROp& m, float (&raw)[16], int r0, in
       const int kq = k0 + 4 * (lane & 7);
       const float* q = base + (long long)r * m.lr;
       if constexpr (FULL) {
-        const f4v t = *reinterpret_cast<const f4v*>(__builtin_assume_aligned(q + kq, 16));
+        const f4u t = *reinterpret_cast<const f4u*>(q + kq);
 #pragma unroll
         for (int e = 0; e < 4; ++e) raw[4 * j + e] = t[e];
       } else {
@@ -1128,11 +1129,18 @@ static int run(int bf16, int M, int N, int K, int batch, FA fa, FB fb, ST st, fl
 }
 
 // ---------------------------------------------------------------- public launchers
-// 1: k is the contiguous dimension of 16-byte aligned rows (vector loads), else 0
+// 1: k is the contiguous dimension of 16-byte aligned rows, else 0
 static int rkind(const MatArg& a) {
   return ((uintptr_t)a.p % 16 == 0 && (!a.alt || (uintptr_t)a.alt % 16 == 0) &&
           (!a.kp || (uintptr_t)a.kp % 16 == 0) && a.sz % 4 == 0 && a.lk == 1 && a.lr % 4 == 0) ? 1 : 0;
 }
+
+// Whether the 32 x 32 tile reads an operand row-coalesced (its vector loads take any
+// float's address): k-contiguous rows, at any alignment -- the flat parameter vector's
+// weights, 101 atoms' logits.  Read in fragment order, one row a lane, such an operand
+// cost more than the product: 2 x 512^3 in bfloat16 18.8 -> 8.4 us, 2 x 2000 x 101 x 512
+// in FP32 20.7 -> 11.2 us.
+static int krows(const MatArg& m) { return m.lk == 1; }
 
 static RMat rmat(const MatArg& m) { return RMat{m.p, m.lr, m.lk, m.sz, m.alt, m.zalt, m.zdiv, m.kp, m.kalt}; }
 static StMat stmat(const OutArg& c) {
@@ -1371,7 +1379,7 @@ int gemm(int bf16, int M, int N, int K, int batch, MatArg A, MatArg B, OutArg C,
     return SQ_EINVAL;
   }
   const StMat out = stmat(C);
-  const int va = rkind(A), vb = rkind(B);
+  const int va = krows(A), vb = krows(B);
   // the copy form does not split K; an operand without FP32 values takes it unsplit
   const bool fp32 = fp32_ok(A) && fp32_ok(B);
   if (bf16 && (!fp32 || want_splits(M, N, K, batch, scratch, scratch_floats) == 1)) {
@@ -1570,7 +1578,7 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     if (bf16) k_gemm_pair_f<true><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);
     else k_gemm_pair_f<false><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);
   } else {
-    const int av0 = rkind(p0.A);
+    const int av0 = krows(p0.A);
     if (bf16 && av0) k_gemm_pair<true, 1><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);
     else if (bf16) k_gemm_pair<true, 0><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);
     else if (av0) k_gemm_pair<false, 1><<<t0 + t1, kThreads, 0, st>>>(q0, q1, t0);

@@ -84,3 +84,35 @@ def test_large_tile_accumulates():
     C0 = torch.randn((Z, M, N), generator=gen, device="cuda")
     C = api.gemm(0, A, B, C=C0.clone(), accumulate=True)
     assert torch.equal(C, api.gemm(0, A, B) + C0)
+
+
+@pytest.mark.parametrize("K", [1, 3, 31, 32, 33, 64, 127, 129, 274])
+@pytest.mark.parametrize("kinds", ["row row1", "row1 row", "row1 row1", "row1 col", "col row1"])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_unaligned_rows_equal_aligned_rows(prec, kinds, K):
+    """k-contiguous rows at any float's address, in the 32 x 32 tile."""
+    print(f"unaligned rows prec={prec} {kinds} K={K}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    z, m, n = 2, 70, 101
+    ops = [_rows(gen, z, r, K, kind) for kind, r in zip(kinds.split(), (m, n))]
+    want = api.gemm(prec, *(_aligned(t) for t in ops))
+    assert torch.equal(api.gemm(prec, *ops), want)
+    for by in (1, 2, 3):   # and a first element off its alignment
+        assert torch.equal(api.gemm(prec, *(_moved(t, by) for t in ops)), want), by
+
+
+def _aligned(t):
+    """t with k-contiguous, 16-byte aligned rows."""
+    z, r, K = t.shape
+    out = torch.zeros((z, r, (K + 3) // 4 * 4), device="cuda")[..., :K]
+    out.copy_(t)
+    return out
+
+
+def _moved(t, by):
+    """t at the same strides, its storage `by` floats off its alignment."""
+    size = sum((n - 1) * s for n, s in zip(t.shape, t.stride())) + 1
+    out = torch.zeros(size + 4, device="cuda")[by:].as_strided(t.shape, t.stride())
+    out.copy_(t)
+    return out

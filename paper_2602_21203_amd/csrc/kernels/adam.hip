@@ -6,6 +6,7 @@
 #include "../common.h"
 #include "bf16.h"
 #include "finish.h"
+#include "partsum.h"
 
 namespace sq {
 
@@ -153,6 +154,8 @@ __device__ __forceinline__ void adam_elem(const AdamArgs& A, const PackArgs& pk,
 // workgroup per 64 parameters of every partial-gradient segment: wave w sums the
 // partial rows w, w + 4, ... of its lane's parameter, the four wave sums are
 // added in wave order (the order colsum() uses), and wave 0 applies the update.
+// Sixteen partial rows of a wave are in flight (four: 39.9 us for the critic's launch at
+// batch 2048, which reads 1024 rows of the encoder's partial gradients; sixteen: 28.9).
 // The rest take 256 * PER consecutive parameters each, skipping the segments.
 template <int PER>
 __global__ __launch_bounds__(256) void k_adam(AdamArgs A, PackArgs pk, GradSegs gs, int seg_blocks, AlphaJob aj,
@@ -180,15 +183,7 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs A, PackArgs pk, GradSegs 
     float sum = 0.f;
     if (j < e.H) {
       const float* pp = e.part + j;
-      int r = wave;
-      for (; r + 12 < e.nrows; r += 16) {
-        float w[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) w[k] = pp[(long long)(r + 4 * k) * e.H];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) sum += w[k];
-      }
-      for (; r < e.nrows; r += 4) sum += pp[(long long)r * e.H];
+      sum = part_rows_sum(pp, e.H, wave, e.nrows);
     }
     sh[wave][lane] = sum;
     __syncthreads();

@@ -41,6 +41,7 @@
 
 #include "../common.h"
 #include "bf16.h"
+#include "partsum.h"
 #include "sample.h"
 #include "lds_tr.h"
 
@@ -402,17 +403,7 @@ __global__ __launch_bounds__(256) void k_enc_reduce(const float* __restrict__ pa
   __shared__ float sh[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long e = (long long)blockIdx.x * 64 + lane;
-  const float* p = part + (e < total ? e : total - 1);
-  float v = 0.f;
-  int w = wave;
-  for (; w + 60 < nwg; w += 64) {
-    float t[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) t[k] = p[(long long)(w + 4 * k) * total];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v += t[k];
-  }
-  for (; w < nwg; w += 4) v += p[(long long)w * total];
+  const float v = part_rows_sum(part + (e < total ? e : total - 1), total, wave, nwg);
   sh[wave][lane] = v;
   __syncthreads();
   if (wave == 0 && e < total)

@@ -31,6 +31,7 @@ void plan_act(const Net& net, int n, Bump& b, ActBufs* w) {
   w->x = b.take<float>((size_t)n * net.img);
   plan_encoder(net, n, b, &w->e, false);
   plan_actor(net, n, b, &w->a, false);
+  w->a.save_rows = 0;
   w->noise = b.take<float>((size_t)n * net.d.action);
 }
 
@@ -148,6 +149,7 @@ static size_t plan_agent(sq_agent* g, char* base) {
   g->act2B = b.take<float>((size_t)2 * B * A);
   g->logp2B = b.take<float>((size_t)2 * B);
   plan_actor(net, 2 * B, b, &g->actor, true);
+  g->actor.save_rows = B;   // the rows of s; those of s' have no backward
   plan_critic(net, B, b, &g->crit, true, 2);
   plan_critic(net, B, b, &g->aux, true);
   g->logits = b.take<float>((size_t)4 * B * N);     // online twins, then target twins

@@ -336,10 +336,11 @@ int encoder32_bwd(const float* x, int n, const float* dfeat, const float* const*
 // batch stride of the first extra block.
 // Batches z >= zalt take the alternative (target-critic) gain and shift; no
 // backward runs through them, so their x-hat and rstd are not stored unless
-// save_alt is set.
+// save_alt is set; nor are those of rows >= save_rows (rows no backward reaches, a third
+// of a launch's bytes).
 struct LnGroups {
   int zalt; const float* g_alt; const float* beta_alt; long long sz_e1; const float* e2_alt;
-  int save_alt = 0;
+  int save_alt = 0, save_rows = 0x7fffffff;
 };
 int ln_act_fwd(const float* pre, long long ld_pre, long long sz_pre, int rows, int H, int batch,
                const float* g, const float* beta, long long sz_par, int act_tanh,

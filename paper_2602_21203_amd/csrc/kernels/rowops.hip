@@ -180,7 +180,7 @@ __device__ __forceinline__ void ln_fwd_row(const float* __restrict__ pre, long l
   }
   float* yr = y + z * sz_y + row * ld_y;
   uint16_t* yhr = yh ? yh + z * sz_y + row * ld_y : nullptr;
-  const bool save = !second || grp.save_alt;
+  const bool save = (!second || grp.save_alt) && row < grp.save_rows;
   if (save) ln_store_row<E, VEC>(xhat + ((long long)z * rows + row) * H, H, lane, xh);
   if (y32) ln_store_row<E, VEC>(yr, H, lane, o);
   if (yhr) ln_store_row_h<E, VEC>(yhr, H, lane, o);

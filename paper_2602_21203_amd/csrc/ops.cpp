@@ -495,6 +495,13 @@ GemmProb actor_trunk_prob(const Net& net, const float* ap, const float* pack, co
   return t;
 }
 
+// one group of rows, of which the first save_rows are kept for a backward
+static LnGroups actor_ln_rows(const ActorBufs& a) {
+  LnGroups g{kNoAlt, nullptr, nullptr, 0, nullptr};
+  g.save_rows = a.save_rows;
+  return g;
+}
+
 int trunks_forward(const Net& net, int bf16, const float* ap, const float* cp, const float* tcp, const float* pack,
                    const float* cpack, const float* tpack, const Layout& L, const float* feat, long long ld_feat,
                    const float* s, long long ld_s, int B, const ActorBufs& a, const CriticBufs& c, hipStream_t st) {
@@ -505,8 +512,9 @@ int trunks_forward(const Net& net, int bf16, const float* ap, const float* cp, c
   const long long a0 = L.actor_begin, c0 = L.critic_begin;
   const Dense& Ta = L.atrunk;
   const Dense& Tc = L.ctrunk;
+  const LnGroups rows = actor_ln_rows(a);
   const LnFwdJob ja = ln_fwd_job(a.pre, P, 0, 2 * B, P, 1, ap + (Ta.g - a0), ap + (Ta.beta - a0), 0, 1, a.X1,
-                                 net.apad, 0, a.t.xhat, a.t.rstd, s, ld_s, S, nullptr, 0, 0);
+                                 net.apad, 0, a.t.xhat, a.t.rstd, s, ld_s, S, nullptr, 0, 0, &rows);
   const LnGroups grp{1, tcp + (Tc.g - c0), tcp + (Tc.beta - c0), (long long)B * ld_s, nullptr};
   const LnFwdJob jc = ln_fwd_job(c.pre, P, (long long)B * P, B, P, 2, cp + (Tc.g - c0), cp + (Tc.beta - c0), 0, 1,
                                  c.X1, net.cpad, (long long)B * net.cpad, c.t.xhat, c.t.rstd, s, ld_s, S, nullptr, 0,
@@ -522,20 +530,21 @@ int actor_forward(const Net& net, int bf16, const float* ap, const float* pack, 
   const long long a0 = L.actor_begin;
   const WRef w{ap, pack, a0};
   const Dense& T = L.atrunk;
+  const LnGroups rows = actor_ln_rows(a);
   if (!trunk_done) {
     const GemmProb t = actor_trunk_prob(net, ap, pack, L, feat, ld_feat, n, a);
     SQ_TRY(gemm(bf16, t.M, t.N, t.K, t.batch, t.A, t.B, t.C, nullptr, 0, st));
     SQ_TRY(ln_act_fwd(a.pre, P, 0, n, P, 1, ap + (T.g - a0), ap + (T.beta - a0), 0, 1, a.X1, ald, 0, a.t.xhat,
-                      a.t.rstd, s, ld_s, d.proprio, nullptr, 0, 0, st));
+                      a.t.rstd, s, ld_s, d.proprio, nullptr, 0, 0, st, &rows));
   }
   SQ_TRY(linear_fwd(bf16, n, H, cin, 1, a.X1, ald, 0, w.W(L.al1.W, L.al1.Wp), w.ld(L.al1.in, L.al1.ldp), 0,
                     ap + (L.al1.b - a0), 0, a.pre, H, 0, st));
   SQ_TRY(ln_act_fwd(a.pre, H, 0, n, H, 1, ap + (L.al1.g - a0), ap + (L.al1.beta - a0), 0, 0, a.g1, H, 0, a.l1.xhat,
-                    a.l1.rstd, nullptr, 0, 0, nullptr, 0, 0, st));
+                    a.l1.rstd, nullptr, 0, 0, nullptr, 0, 0, st, &rows));
   SQ_TRY(linear_fwd(bf16, n, H, H, 1, a.g1, H, 0, w.W(L.al2.W, L.al2.Wp), w.ld(L.al2.in, L.al2.ldp), 0,
                     ap + (L.al2.b - a0), 0, a.pre, H, 0, st));
   SQ_TRY(ln_act_fwd(a.pre, H, 0, n, H, 1, ap + (L.al2.g - a0), ap + (L.al2.beta - a0), 0, 0, a.g2, H, 0, a.l2.xhat,
-                    a.l2.rstd, nullptr, 0, 0, nullptr, 0, 0, st));
+                    a.l2.rstd, nullptr, 0, 0, nullptr, 0, 0, st, &rows));
   MatArg X{a.g2, H, 1, 0};
   MatArg Wm{w.W(L.aout.W, L.aout.Wp), w.ld(L.aout.in, L.aout.ldp), 1, 0};
   return gemm_tanh_gauss(bf16, n, A, H, X, Wm, ap + (L.aout.b - a0), eps, lo, hi, action, logp, a.save, a.head, st,

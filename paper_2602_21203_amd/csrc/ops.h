@@ -105,6 +105,8 @@ struct ActorBufs {
   // nullable: the sampled actions of rows >= xact_row0 are also written here
   // (row stride ld_xact), straight into a critic's input rows
   float* xact = nullptr; long long ld_xact = 0; int xact_row0 = 0;
+  // rows a backward may read: x-hat and rstd of the others are not stored
+  int save_rows = 0x7fffffff;
 };
 void plan_actor(const Net& net, int n, Bump& b, ActorBufs* a, bool with_bwd);
 // ap: base of the actor block; pack: the whole packed-weight buffer (nullable);

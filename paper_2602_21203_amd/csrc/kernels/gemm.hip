@@ -724,6 +724,15 @@ __global__ __launch_bounds__(kThreads) void k_gemm_r(RMat fa, RMat fb, ST st, St
   gemm_tile<BF16, AV, BV, ST, SPLIT>(fa, fb, st, sp, M, N, K, kchunk, bx, by, bz, lds);
 }
 
+// Tile i of the `tiles` of a product's part of a launch, in the XCDs' order.  Taken
+// where it was faster: the pairs of FP32 operands (2 x 2000 rows, the first layer's 57.7 ->
+// 55.3 us) and those with the 64 x 64 tile (batch 2048: 22.8 + 15.2 -> 21.8 + 13.6 us), not
+// the others on copies (batch 2048's first layer 19.3 -> 20.6 us).
+template <class P>
+__device__ __forceinline__ void pair_tile(const P& p, int i, int tiles, int& bx, int& by, int& bz) {
+  tile_of(i, p.gx, p.gy, tiles / (p.gx * p.gy), bx, by, bz);
+}
+
 // Two independent products in one launch (the input and weight gradients of one
 // layer): workgroups [0, tiles0) take problem 0 (A row-coalesced when AV0, else
 // k-strided; k-strided B), the rest problem 1 (both k-strided).
@@ -736,14 +745,14 @@ __global__ __launch_bounds__(kThreads) void k_gemm_pair(RProb p0, RProb p1, int 
   constexpr int L0 = gemm_lds_bytes<BF16, AV0, 0>(), L1 = gemm_lds_bytes<BF16, 0, 0>();
   __shared__ __attribute__((aligned(16))) char lds[L0 > L1 ? L0 : L1];
   const StPart none{nullptr, 0, 0, 1};
-  int b = blockIdx.x;
+  const int b = blockIdx.x;
+  int bx, by, bz;
   if (b < tiles0) {
-    gemm_tile<BF16, AV0, 0, StMat, false>(p0.a, p0.b, p0.st, none, p0.M, p0.N, p0.K, p0.K, b % p0.gx,
-                                          (b / p0.gx) % p0.gy, b / (p0.gx * p0.gy), lds);
+    pair_tile(p0, b, tiles0, bx, by, bz);
+    gemm_tile<BF16, AV0, 0, StMat, false>(p0.a, p0.b, p0.st, none, p0.M, p0.N, p0.K, p0.K, bx, by, bz, lds);
   } else {
-    b -= tiles0;
-    gemm_tile<BF16, 0, 0, StMat, false>(p1.a, p1.b, p1.st, none, p1.M, p1.N, p1.K, p1.K, b % p1.gx,
-                                        (b / p1.gx) % p1.gy, b / (p1.gx * p1.gy), lds);
+    pair_tile(p1, b - tiles0, (int)gridDim.x - tiles0, bx, by, bz);
+    gemm_tile<BF16, 0, 0, StMat, false>(p1.a, p1.b, p1.st, none, p1.M, p1.N, p1.K, p1.K, bx, by, bz, lds);
   }
 }
 
@@ -1021,13 +1030,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm_pair_big(RProb p0, RProb p
   constexpr int L0 = BigLds<BF16>::BYTES, L1 = gemm_lds_bytes<BF16, 0, 0>();
   __shared__ __attribute__((aligned(16))) char lds[L0 > L1 ? L0 : L1];
   const int b = blockIdx.x;
+  int bx, by, bz;
   if (b < t1) {
     const StPart none{nullptr, 0, 0, 1};
-    gemm_tile<BF16, 0, 0, StMat, false>(p1.a, p1.b, p1.st, none, p1.M, p1.N, p1.K, p1.K, b % p1.gx,
-                                        (b / p1.gx) % p1.gy, b / (p1.gx * p1.gy), lds);
+    pair_tile(p1, b, t1, bx, by, bz);
+    gemm_tile<BF16, 0, 0, StMat, false>(p1.a, p1.b, p1.st, none, p1.M, p1.N, p1.K, p1.K, bx, by, bz, lds);
   } else {
-    int bx, by, bz;
-    tile_of(b - t1, p0.gx, p0.gy, ((int)gridDim.x - t1) / (p0.gx * p0.gy), bx, by, bz);
+    pair_tile(p0, b - t1, (int)gridDim.x - t1, bx, by, bz);
     big_tile_f<BF16, KA, KB>(p0.a, p0.b, p0.st, p0.M, p0.N, p0.K, bx, by, bz, lds);
   }
 }
@@ -1036,12 +1045,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_gemm_pair_big_h(HProb p0, HProb
   constexpr int L0 = BigLds<true>::BYTES, L1 = hgemm_lds_bytes<false>();
   __shared__ __attribute__((aligned(16))) char lds[L0 > L1 ? L0 : L1];
   const int b = blockIdx.x;
+  int bx, by, bz;
   if (b < t1) {
-    gemm_tile_h<false, true, true, false, StMat>(p1.a, p1.b, p1.st, p1.M, p1.N, p1.K, b % p1.gx, (b / p1.gx) % p1.gy,
-                                                 b / (p1.gx * p1.gy), lds);
+    pair_tile(p1, b, t1, bx, by, bz);
+    gemm_tile_h<false, true, true, false, StMat>(p1.a, p1.b, p1.st, p1.M, p1.N, p1.K, bx, by, bz, lds);
   } else {
-    int bx, by, bz;
-    tile_of(b - t1, p0.gx, p0.gy, ((int)gridDim.x - t1) / (p0.gx * p0.gy), bx, by, bz);
+    pair_tile(p0, b - t1, (int)gridDim.x - t1, bx, by, bz);
     big_tile_h<false, true>(p0.a, p0.b, p0.st, p0.M, p0.N, p0.K, bx, by, bz, lds);
   }
 }

@@ -260,6 +260,16 @@ long long copy_products();
 int gemm_tanh_gauss(int bf16, int n, int A, int K, MatArg X, MatArg W, const float* bias, const float* eps, float lo,
                     float hi, float* action, float* logp, float* save, float* head, hipStream_t st,
                     float* xact = nullptr, long long ld_xact = 0, int xact_row0 = 0);
+// Products whose input rows are [act(LayerNorm(pre)) | e1], normalised inside the launch
+// (W: k-contiguous rows); where gemm_ln_ok says so, with the bits of the separate launches.
+struct LnIn {
+  const float* pre; long long ld_pre; const float* g; const float* beta; int H, act_tanh;
+  const float* e1; long long ld_e1; int w1;
+};
+bool gemm_ln_ok(const LnIn& x, int n);
+int gemm_ln(int bf16, int n, int N, const LnIn& x, MatArg W, OutArg C, hipStream_t st);
+int gemm_ln_tanh_gauss(int bf16, int n, int A, const LnIn& x, MatArg W, const float* bias, const float* eps, float lo,
+                       float hi, float* action, float* logp, float* save, float* head, hipStream_t st);
 struct GemmProb {
   int M, N, K, batch; MatArg A, B; OutArg C;
 };

@@ -25,6 +25,7 @@
 #include "bf16.h"
 #include "tgauss.h"
 #include "lds_tr.h"
+#include "ln_row.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -435,12 +436,21 @@ template <bool BF16> struct RLds {
   static constexpr int WAVE = 2 * kRG * TILE;             // two operands for each chunk of a group
 };
 
+// An operand whose rows the workgroup has normalised itself (V = 2 below): its 32 rows of
+// the whole contraction in LDS, zeros from K to the chunk's end.
+constexpr int kLnPanelK = 544;   // 512, or 256 + copied columns, in whole chunks
+template <bool BF16> struct LnPanel {
+  using T = typename RLds<BF16>::T;
+  static constexpr int LD = kLnPanelK + (BF16 ? 8 : 4);
+  static constexpr int BYTES = 32 * LD * (int)sizeof(T);
+};
+
 template <bool BF16> struct RFrag;
 template <> struct RFrag<true> { bf16x8 v[2]; };
 template <> struct RFrag<false> { float v[2][8]; };
 
 // raw chunk of one operand: V = 1: raw[4 j + e] = row r0 + 8 j + lane / 8, k = k0 + 4 (lane % 8) + e;
-// V = 0: raw[8 i + e] = row r0 + 16 i + li, k = k0 + 8 lq + e.  Rows past the end are
+// V = 0: raw[8 i + e] = row r0 + 16 i + li, k = k0 + 8 lq + e; V = 2: nothing.  Rows past the end are
 // clamped into the matrix (computed on valid data, never stored).  FULL: the chunk
 // lies inside the contraction, else k >= kend reads as zero.
 // One operand of one batch: rows at base (k < kalt) or kbase (k >= kalt, read at k - kalt).
@@ -450,13 +460,14 @@ struct ROp {
 
 template <int V, bool FULL>
 __device__ __forceinline__ void rload(const ROp& m, float (&raw)[16], int r0, int rows, int k0, int kend, int lane) {
+  if constexpr (V == 2) return;
   const float* base = m.base;
   if (k0 >= m.kalt) {   // uniform: kalt is a multiple of the chunk
     base = m.kbase;
     k0 -= m.kalt;
     kend -= m.kalt;
   }
-  if constexpr (V) {
+  if constexpr (V == 1) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int r = min(r0 + 8 * j + (lane >> 3), rows - 1);
@@ -495,13 +506,13 @@ __device__ __forceinline__ void rload(const ROp& m, float (&raw)[16], int r0, in
   }
 }
 
-// raw chunk -> MFMA fragments.  V = 1 goes through the wave's LDS tile in two
+// raw chunk -> MFMA fragments (V = 2: of the panel, from its column k).  V = 1 goes through the wave's LDS tile in two
 // steps, so that the LDS round trips of a whole register group overlap: stage()
 // writes the chunk, frag() reads the fragments back after the group's single wait.
 template <bool BF16, int V>
 __device__ __forceinline__ void stage(const float (&raw)[16], typename RLds<BF16>::T* tile, int lane) {
   using LL = RLds<BF16>;
-  if constexpr (V) {
+  if constexpr (V == 1) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       auto* dst = tile + (8 * j + (lane >> 3)) * LL::LDT + 4 * (lane & 7);
@@ -523,9 +534,10 @@ __device__ __forceinline__ void frag(const float (&raw)[16], const typename RLds
   using LL = RLds<BF16>;
   const int li = lane & 15, lq = lane >> 4;
   if constexpr (V) {
+    constexpr int LD = V == 2 ? LnPanel<BF16>::LD : LL::LDT;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const auto* src = tile + (16 * i + li) * LL::LDT + 8 * lq;
+      const auto* src = tile + (16 * i + li) * LD + 8 * lq;
       if constexpr (BF16) {
         f.v[i] = *reinterpret_cast<const bf16x8*>(src);
       } else {
@@ -614,10 +626,13 @@ constexpr int gemm_lds_bytes() {
   return TILE_BYTES > RED_BYTES ? TILE_BYTES : RED_BYTES;
 }
 
-// one 32 x 32 output tile (bx, by) of batch / split index bz
-template <bool BF16, int AV, int BV, class ST, bool SPLIT>
+// one 32 x 32 output tile (bx, by) of batch / split index bz; AV = 2: before() fills the
+// A panel, once B's first chunks have been requested
+struct NoPanel { __device__ __forceinline__ void operator()() const {} };
+template <bool BF16, int AV, int BV, class ST, bool SPLIT, class BEFORE = NoPanel>
 __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const ST& st, const StPart& sp, int M,
-                                          int N, int K, int kchunk, int bx, int by, int bz, char* lds) {
+                                          int N, int K, int kchunk, int bx, int by, int bz, char* lds,
+                                          const BEFORE& before = {}, const typename RLds<BF16>::T* panel = nullptr) {
   using LL = RLds<BF16>;
   using T = typename LL::T;
   constexpr int KC = kRKC, G = kRG;
@@ -655,7 +670,7 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
     }
   };
   // a group's chunks: stage all (V = 1), one wait, then fragments and products
-  auto mult = [&](int buf) {
+  auto mult = [&](int g, int buf) {
     if constexpr (AV || BV) {
 #pragma unroll
       for (int c = 0; c < G; ++c) {
@@ -667,20 +682,20 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
 #pragma unroll
     for (int c = 0; c < G; ++c) {
       RFrag<BF16> fa_, fb_;
-      frag<BF16, AV>(ra[buf][c], wt + (2 * c) * LL::TILE, lane, fa_);
+      frag<BF16, AV>(ra[buf][c], AV == 2 ? panel + wb + (g * G + c) * KC : wt + (2 * c) * LL::TILE, lane, fa_);
       frag<BF16, BV>(rb[buf][c], wt + (2 * c + 1) * LL::TILE, lane, fb_);
       rmma<BF16>(fa_, fb_, acc);
     }
     if constexpr (AV || BV) asm volatile("" ::: "memory");
   };
-  auto chunk = [&](const float (&a)[16], const float (&b)[16]) {
+  auto chunk = [&](const float (&a)[16], const float (&b)[16], int k) {
     RFrag<BF16> fa_, fb_;
     if constexpr (AV || BV) {
       stage<BF16, AV>(a, wt, lane);
       stage<BF16, BV>(b, wt + LL::TILE, lane);
       lds_wave_sync();
     }
-    frag<BF16, AV>(a, wt, lane, fa_);
+    frag<BF16, AV>(a, AV == 2 ? panel + k : wt, lane, fa_);
     frag<BF16, BV>(b, wt + LL::TILE, lane, fb_);
     rmma<BF16>(fa_, fb_, acc);
     if constexpr (AV || BV) asm volatile("" ::: "memory");
@@ -688,11 +703,12 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
   // two register groups in flight: group g + 1 loads while group g multiplies
   if (ngf > 0) load(0, 0);
   if (ngf > 1) load(1, 1);
+  before();
   for (int g = 0; g < ngf; g += 2) {
-    mult(0);
+    mult(g, 0);
     if (g + 2 < ngf) load(g + 2, 0);
     if (g + 1 < ngf) {
-      mult(1);
+      mult(g + 1, 1);
       if (g + 3 < ngf) load(g + 3, 1);
     }
   }
@@ -702,13 +718,13 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
     float ta[16], tb[16];
     rload<AV, true>(oa, ta, m0, M, k0, we, lane);
     rload<BV, true>(ob, tb, n0, N, k0, we, lane);
-    chunk(ta, tb);
+    chunk(ta, tb, k0);
   }
   if (k0 < we) {
     float ta[16], tb[16];
     rload<AV, false>(oa, ta, m0, M, k0, we, lane);
     rload<BV, false>(ob, tb, n0, N, k0, we, lane);
-    chunk(ta, tb);
+    chunk(ta, tb, k0);
   }
 
   tile_out<ST, SPLIT>(acc, st, sp, M, N, m0, n0, z, split, wave, lane, lds);
@@ -722,6 +738,63 @@ __global__ __launch_bounds__(kThreads) void k_gemm_r(RMat fa, RMat fb, ST st, St
   tile_of(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z, bx, by,
           bz);
   gemm_tile<BF16, AV, BV, ST, SPLIT>(fa, fb, st, sp, M, N, K, kchunk, bx, by, bz, lds);
+}
+
+// A product whose input rows are the LayerNorm + activation of `pre` (and copied
+// columns): each workgroup normalises the 32 rows of its tile into an LDS panel (the
+// LayerNorm kernels' arithmetic, bit for bit) while its first weights are on their way.
+// Every column tile repeats that, which costs less than a launch as long as the rows are
+// few (kLnGemmRows).
+struct LnRows {
+  const float* pre; long long ld_pre; const float* g; const float* beta; int H, act_tanh;
+  const float* e1; long long ld_e1; int w1;
+};
+
+template <bool BF16, int E>
+__device__ __forceinline__ void ln_panel(const LnRows& j, int m0, int M, typename RLds<BF16>::T* panel) {
+  using P = LnPanel<BF16>;
+  using T = typename P::T;
+  constexpr int R = 4;   // rows of a wave in flight
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int K = 64 * E + j.w1, kp = (K + kRKC - 1) / kRKC * kRKC;
+  float gv[E], bv[E];
+  ln_load_par<E, true>(j.g, 64 * E, lane, gv);
+  ln_load_par<E, true>(j.beta, 64 * E, lane, bv);
+  for (int i0 = 0; i0 < 32 / 4 && m0 + 4 * i0 + wave < M; i0 += R) {
+    float v[R][E];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      ln_load_row<E, true>(j.pre + (long long)min(m0 + 4 * (i0 + i) + wave, M - 1) * j.ld_pre, 64 * E, lane, v[i]);
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = 4 * (i0 + i) + wave;
+      if (m0 + r >= M) break;
+      float xh[E], o[E];
+      ln_row<E, true>(v[i], gv, bv, 64 * E, lane, j.act_tanh, xh, o);
+      T* row = panel + r * P::LD;
+#pragma unroll
+      for (int c = 0; c < E / 4; ++c) {
+        typedef T t4 __attribute__((ext_vector_type(4)));
+        *reinterpret_cast<t4*>(row + 256 * c + 4 * lane) =
+            t4{(T)o[4 * c], (T)o[4 * c + 1], (T)o[4 * c + 2], (T)o[4 * c + 3]};
+      }
+      for (int e = lane; e < kp - 64 * E; e += 64)
+        row[64 * E + e] = e < j.w1 ? (T)j.e1[(long long)(m0 + r) * j.ld_e1 + e] : (T)0.f;
+    }
+  }
+  __syncthreads();
+}
+
+template <bool BF16, int E, class ST>
+__global__ __launch_bounds__(kThreads) void k_gemm_ln(LnRows ln, RMat fb, ST st, int M, int N, int K) {
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds_bytes<BF16, 2, 1>()];
+  __shared__ __attribute__((aligned(16))) char pan[LnPanel<BF16>::BYTES];
+  auto* panel = reinterpret_cast<typename RLds<BF16>::T*>(pan);
+  const RMat none{nullptr, 0, 0, 0, nullptr, kNoAlt, 1, nullptr, kNoAlt};
+  const StPart nosp{nullptr, 0, 0, 1};
+  const int m0 = (int)blockIdx.x * kTile;
+  gemm_tile<BF16, 2, 1, ST, false>(none, fb, st, nosp, M, N, K, K, blockIdx.x, blockIdx.y, 0, lds,
+                                   [&] { ln_panel<BF16, E>(ln, m0, M, panel); }, panel);
 }
 
 // Tile i of the `tiles` of a product's part of a launch, in the XCDs' order.  Taken
@@ -1408,6 +1481,40 @@ int gemm(int bf16, int M, int N, int K, int batch, MatArg A, MatArg B, OutArg C,
   if (va) return run_r<false, 1, 0>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
   if (vb) return run_r<false, 0, 1>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
   return run_r<false, 0, 0>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
+}
+
+// Up to here a wave normalises its rows of a tile in one flight.  A policy query with
+// three separate LayerNorm launches / normalising in the products, bfloat16 and FP32, us:
+//   1 row    37.7 / 26.3   56.0 / 47.4        32 rows  38.5 / 41.4   61.8 / 65.0
+//   8 rows   37.9 / 28.7   59.1 / 51.8       512 rows  43.9 / 48.2   68.7 / 75.9
+constexpr int kLnGemmRows = 16;
+
+bool gemm_ln_ok(const LnIn& x, int n) {
+  return n > 0 && n <= kLnGemmRows && (x.H == 256 || x.H == 512) && x.H + x.w1 <= kLnPanelK &&
+         (uintptr_t)x.pre % 16 == 0 && x.ld_pre % 4 == 0;
+}
+
+template <class ST>
+static int launch_gemm_ln(int bf16, int n, int N, const LnIn& x, const MatArg& W, const ST& st, hipStream_t stream) {
+  const LnRows j{x.pre, x.ld_pre, x.g, x.beta, x.H, x.act_tanh, x.e1, x.ld_e1, x.w1};
+  const dim3 grid(cdiv(n, kTile), cdiv(N, kTile));
+  const RMat w = rmat(W);
+  const int K = x.H + x.w1;
+  if (bf16 && x.H == 256) k_gemm_ln<true, 4, ST><<<grid, kThreads, 0, stream>>>(j, w, st, n, N, K);
+  else if (bf16) k_gemm_ln<true, 8, ST><<<grid, kThreads, 0, stream>>>(j, w, st, n, N, K);
+  else if (x.H == 256) k_gemm_ln<false, 4, ST><<<grid, kThreads, 0, stream>>>(j, w, st, n, N, K);
+  else k_gemm_ln<false, 8, ST><<<grid, kThreads, 0, stream>>>(j, w, st, n, N, K);
+  return launch_status("gemm_ln");
+}
+
+int gemm_ln(int bf16, int n, int N, const LnIn& x, MatArg W, OutArg C, hipStream_t st) {
+  return launch_gemm_ln(bf16, n, N, x, W, stmat(C), st);
+}
+
+int gemm_ln_tanh_gauss(int bf16, int n, int A, const LnIn& x, MatArg W, const float* bias, const float* eps, float lo,
+                       float hi, float* action, float* logp, float* save, float* head, hipStream_t st) {
+  const StTanhGauss tg{bias, eps, lo, hi, action, logp, save, head, A, nullptr, 0, 0, nullptr};
+  return launch_gemm_ln(bf16, n, 2 * A, x, W, tg, st);
 }
 
 int gemm_tanh_gauss(int bf16, int n, int A, int K, MatArg X, MatArg W, const float* bias, const float* eps, float lo,

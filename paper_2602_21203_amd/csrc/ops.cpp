@@ -531,6 +531,21 @@ int actor_forward(const Net& net, int bf16, const float* ap, const float* pack, 
   const WRef w{ap, pack, a0};
   const Dense& T = L.atrunk;
   const LnGroups rows = actor_ln_rows(a);
+  const LnIn x1{a.pre, P, ap + (T.g - a0), ap + (T.beta - a0), P, 1, s, ld_s, d.proprio};
+  const LnIn x2{a.g1, H, ap + (L.al1.g - a0), ap + (L.al1.beta - a0), H, 0, nullptr, 0, 0};
+  const LnIn x3{a.pre, H, ap + (L.al2.g - a0), ap + (L.al2.beta - a0), H, 0, nullptr, 0, 0};
+  if (a.save_rows == 0 && !trunk_done && 2 * A <= 32 && a.head && !a.xact && gemm_ln_ok(x1, n) && gemm_ln_ok(x2, n) &&
+      gemm_ln_ok(x3, n)) {
+    // nothing is kept for a backward, and few rows: each product normalises its own
+    // input (the layers' outputs before their LayerNorm alternate between pre and g1)
+    const GemmProb t = actor_trunk_prob(net, ap, pack, L, feat, ld_feat, n, a);
+    SQ_TRY(gemm(bf16, t.M, t.N, t.K, t.batch, t.A, t.B, t.C, nullptr, 0, st));
+    auto W = [&](const auto& D) { return MatArg{w.W(D.W, D.Wp), w.ld(D.in, D.ldp), 1, 0}; };
+    SQ_TRY(gemm_ln(bf16, n, H, x1, W(L.al1), OutArg{a.g1, H, 0, ap + (L.al1.b - a0), 0, 0, 0}, st));
+    SQ_TRY(gemm_ln(bf16, n, H, x2, W(L.al2), OutArg{a.pre, H, 0, ap + (L.al2.b - a0), 0, 0, 0}, st));
+    return gemm_ln_tanh_gauss(bf16, n, A, x3, W(L.aout), ap + (L.aout.b - a0), eps, lo, hi, action, logp, a.save,
+                              a.head, st);
+  }
   if (!trunk_done) {
     const GemmProb t = actor_trunk_prob(net, ap, pack, L, feat, ld_feat, n, a);
     SQ_TRY(gemm(bf16, t.M, t.N, t.K, t.batch, t.A, t.B, t.C, nullptr, 0, st));

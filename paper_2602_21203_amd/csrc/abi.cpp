@@ -127,10 +127,7 @@ int encoder_fwd(const sq_dims* dims, sq_prec prec, const float* enc_params, cons
   EncWs w;
   plan_op(net, SQ_OP_ENCODER, n, ws_base(ws), &w);
   hipStream_t st = (hipStream_t)stream;
-  SQ_TRY_HIP(hipMemcpyAsync(w.x, x, (size_t)n * net.img * 4, hipMemcpyDeviceToDevice, st));
-  SQ_TRY(encoder_forward(net, prec == SQ_BF16, enc_params, L, w.x, n, w.e, st));
-  SQ_TRY_HIP(hipMemcpyAsync(feat, w.e.h[dims->n_conv - 1], (size_t)n * net.flat * 4, hipMemcpyDeviceToDevice, st));
-  return SQ_OK;
+  return encoder_forward(net, prec == SQ_BF16, enc_params, L, x, n, w.e, st, false, w.x, feat);
 }
 
 int encoder_bwd(const sq_dims* dims, sq_prec prec, const float* enc_params, const void* ws, const float* dfeat, int n,

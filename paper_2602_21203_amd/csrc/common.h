@@ -316,10 +316,11 @@ bool encoder_fused_act_ok(const uint8_t* frames, int H, int W, int C, int F, int
 int encoder_fused_fwd_act(const uint8_t* frames, int n, const float* wp, const float* const* b, float* const* h,
                           unsigned long long seed, unsigned long long request_id, int noise_n, float* noise,
                           hipStream_t st);
-// inner: the inner layers are wanted too (the FP32 form always writes them); hh (nullable, bfloat16 form
-// only): the last layer's output is also written there rounded to bfloat16
+// inner: the inner layers are wanted too (the FP32 form always writes them).  bfloat16 form only, nullable:
+// hh, the last layer's output rounded to bfloat16; xsave, a copy of x; feat2, one of the last layer's output
 int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* wp,
-                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh = nullptr);
+                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh = nullptr,
+                      float* xsave = nullptr, float* feat2 = nullptr);
 // the order of a partial gradient's elements (bfloat16 form); W: flat offsets of the conv weights
 EncOrder encoder_fused_order(int C, int F, int n_conv, const long long* W);
 // partial gradients of every workgroup in part, their ordered sum in grad[0, total)
@@ -332,10 +333,11 @@ int encoder_reduce(const float* part, int rows, long long total, float* grad, co
 // encoder32.hip: the FP32 encoder on 32 x 32 inputs; every activation NCHW, as the
 // general convolutions keep them (and the same forward bits).  The forward returns
 // kNotApplicable when x or the last activation is not 16-byte aligned; everything else
-// lies in a workspace (256-byte aligned).  part: n * total floats
+// lies in a workspace (256-byte aligned).  xsave, feat2 (nullable, 16-byte aligned):
+// copies of x and of the last activation.  part: n * total floats
 bool encoder32_ok(int C, int F, int n_conv, int side);
 int encoder32_fwd(const float* x, int n, const float* const* W, const float* const* b, float* const* h,
-                  hipStream_t st);
+                  float* xsave, float* feat2, hipStream_t st);
 int encoder32_bwd(const float* x, int n, const float* dfeat, const float* const* W, const float* const* h,
                   const long long* Woff, const long long* boff, long long total, float* part, float* grad,
                   hipStream_t st);

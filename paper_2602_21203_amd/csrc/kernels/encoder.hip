@@ -473,12 +473,13 @@ struct WFrag {
 
 // forward layer l of one image: in [HI][HI][PS] (bfloat16, LDS) -> post-ReLU
 // out_lds [HO][HO][F + 8] (bfloat16) and, unless it is null, out_g (FP32, [pixel][F]);
-// the last layer goes to out_lds_f (LDS) and from there, in NCHW order, to out_g and
-// out_h.  w: the wave's weight fragments (its one column tile).
+// the last layer goes to out_lds_f (LDS) and from there, in NCHW order, to out_g, out_h
+// and out_2.  w: the wave's weight fragments (its one column tile).
 template <int C, int F, int l, int SD, bool LAST, int NT>
 __device__ __forceinline__ void conv_fwd_layer_b(const __bf16* in, __bf16* out_lds, float* __restrict__ out_g,
                                                  const WFrag<C, F, l, SD>& w, float* out_lds_f = nullptr,
-                                                 uint16_t* __restrict__ out_h = nullptr) {
+                                                 uint16_t* __restrict__ out_h = nullptr,
+                                                 float* __restrict__ out_2 = nullptr) {
   using Y = LB<C, F, l, SD>;
   constexpr int RT = (Y::P + 15) / 16, CT = F / 16, NW = NT / 64;
   constexpr int PSO = F + 8;
@@ -517,6 +518,7 @@ __device__ __forceinline__ void conv_fwd_layer_b(const __bf16* in, __bf16* out_l
       const float v = out_lds_f[e];
       out_g[e] = v;
       if (out_h) out_h[e] = bf16_bits(v);
+      if (out_2) out_2[e] = v;
     }
   }
 }
@@ -534,6 +536,8 @@ struct EncFwdArgs {
   // inner layers of images below nsave (the backward's) are stored
   float* h[3]; int nsave; uint16_t* hh;
   const uint8_t* obs; const uint8_t* next_obs; SampleArgs sa; ActNoise noise; int lead; float* xout;
+  // kEncX, nullable: x is also copied here, the features also written there
+  float* xsave; float* feat2;
 };
 
 // One image's source, requested a whole image ahead of its use.  Frames (SQK x SQK
@@ -672,18 +676,21 @@ __global__ __launch_bounds__(NT, SQK <= 1 && SD == 16 ? 3 : 2) void k_encoder_fw
     }
   }
   // the requested image into LDS: its frame, or x as [pixel][channel] bfloat16
-  auto stage = [&]() {
+  auto stage = [&](int img) {
     if constexpr (SQK > 0) {
       im.store(buf);
     } else {
 #pragma unroll
       for (int i = 0; i < I::R; ++i) {
         const int e = (int)threadIdx.x + NT * i, c = e / (SD * SD), p = e - c * SD * SD;
-        if (I::N % NT == 0 || e < I::N) lx[p * L0::PS + c] = (__bf16)im.v[i];
+        if (I::N % NT == 0 || e < I::N) {
+          lx[p * L0::PS + c] = (__bf16)im.v[i];
+          if (a.xsave) a.xsave[(long long)img * I::N + e] = im.v[i];
+        }
       }
     }
   };
-  stage();
+  stage(first);
   lds_barrier();
   for (int img = first; img < a.n; img += stride) {
     const bool save = img < a.nsave, more = img + stride < a.n;
@@ -716,11 +723,12 @@ __global__ __launch_bounds__(NT, SQK <= 1 && SD == 16 ? 3 : 2) void k_encoder_fw
       lds_barrier();
     }
     // (before the features' stores, which a wait for the loads would include)
-    if (more) stage();
+    if (more) stage(img + stride);
     float* out = a.h[NC - 1] + io * F * LL::P;
     uint16_t* oh = a.hh ? a.hh + io * F * LL::P : nullptr;
-    if constexpr (NC > 2) conv_fwd_layer_b<C, F, 2, SD, true, NT>(la1, nullptr, out, w2, lout, oh);
-    else conv_fwd_layer_b<C, F, 1, SD, true, NT>(la0, nullptr, out, w1, lout, oh);
+    float* o2 = SRC == kEncX && a.feat2 ? a.feat2 + io * F * LL::P : nullptr;
+    if constexpr (NC > 2) conv_fwd_layer_b<C, F, 2, SD, true, NT>(la1, nullptr, out, w2, lout, oh, o2);
+    else conv_fwd_layer_b<C, F, 1, SD, true, NT>(la0, nullptr, out, w1, lout, oh, o2);
   }
 }
 
@@ -1093,12 +1101,14 @@ constexpr int enc_bwd_g(int side) { return side == 16 ? kEncBwdG : 1; }
 
 template <bool BF16, int C, int F, int NC, int SD>
 static int enc_fwd_t(const float* x, int n, const float* wp, const float* const* b, float* const* h, bool inner,
-                     uint16_t* hh, hipStream_t st) {
+                     uint16_t* hh, hipStream_t st, float* xsave = nullptr, float* feat2 = nullptr) {
   if constexpr (BF16) {
     EncFwdArgs a{};
     a.x = x;
     a.n = n;
     a.nsave = inner ? n : 0;
+    a.xsave = xsave;
+    a.feat2 = feat2;
     a.wp = reinterpret_cast<const __bf16*>(wp);
     for (int i = 0; i < NC; ++i) {
       a.b[i] = b[i];
@@ -1209,17 +1219,18 @@ int encoder_fused_prep(int bf16, int C, int F, int n_conv, const float* const* W
 }
 
 int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float* x, int n, const float* wp,
-                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh) {
+                      const float* const* b, float* const* h, bool inner, hipStream_t st, uint16_t* hh,
+                      float* xsave, float* feat2) {
   if (n <= 0) return SQ_OK;
-  if (hh && !bf16) {
-    set_error("encoder_fused_fwd: the feature's bfloat16 copy is written by the bfloat16 form only");
+  if ((hh || xsave || feat2) && !bf16) {
+    set_error("encoder_fused_fwd: copies are written by the bfloat16 form only");
     return SQ_EINVAL;
   }
-  if (side == 32) return enc_fwd_t<true, 9, 32, 3, 32>(x, n, wp, b, h, inner, hh, st);
+  if (side == 32) return enc_fwd_t<true, 9, 32, 3, 32>(x, n, wp, b, h, inner, hh, st, xsave, feat2);
   if (C == 9 && F == 32 && n_conv == 3)
-    return bf16 ? enc_fwd_t<true, 9, 32, 3, 16>(x, n, wp, b, h, inner, hh, st)
+    return bf16 ? enc_fwd_t<true, 9, 32, 3, 16>(x, n, wp, b, h, inner, hh, st, xsave, feat2)
                 : enc_fwd_t<false, 9, 32, 3, 16>(x, n, wp, b, h, inner, nullptr, st);
-  return bf16 ? enc_fwd_t<true, 3, 16, 2, 16>(x, n, wp, b, h, inner, hh, st)
+  return bf16 ? enc_fwd_t<true, 3, 16, 2, 16>(x, n, wp, b, h, inner, hh, st, xsave, feat2)
               : enc_fwd_t<false, 3, 16, 2, 16>(x, n, wp, b, h, inner, nullptr, st);
 }
 

@@ -42,9 +42,13 @@ template <int C, int F, int SD, int l> struct Lay {
 __device__ __forceinline__ v4f mfma(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // n floats (a multiple of 4, 16-byte aligned) between global memory and LDS
-__device__ __forceinline__ void copy4(const float* __restrict__ src, float* dst, int n) {
-  for (int e = 4 * (int)threadIdx.x; e < n; e += 4 * kT)
-    *reinterpret_cast<v4f*>(dst + e) = *reinterpret_cast<const v4f*>(src + e);
+// (and, when dst2 is given, there too)
+__device__ __forceinline__ void copy4(const float* __restrict__ src, float* dst, int n, float* dst2 = nullptr) {
+  for (int e = 4 * (int)threadIdx.x; e < n; e += 4 * kT) {
+    const v4f v = *reinterpret_cast<const v4f*>(src + e);
+    *reinterpret_cast<v4f*>(dst + e) = v;
+    if (dst2) *reinterpret_cast<v4f*>(dst2 + e) = v;
+  }
 }
 __device__ __forceinline__ void zero4(float* dst, int n) {
   for (int e = 4 * (int)threadIdx.x; e < n; e += 4 * kT) *reinterpret_cast<v4f*>(dst + e) = v4f{0.f, 0.f, 0.f, 0.f};
@@ -120,7 +124,8 @@ struct Ptrs { const float* W[3]; const float* b[3]; };
 struct Acts { float* h[3]; };
 
 template <int C, int F, int SD>
-__global__ __launch_bounds__(kT) void k_encoder32_fwd(const float* __restrict__ x, Ptrs w, Acts h) {
+__global__ __launch_bounds__(kT) void k_encoder32_fwd(const float* __restrict__ x, Ptrs w, Acts h, float* xsave,
+                                                      float* feat2) {
   using L0 = Lay<C, F, SD, 0>;
   using L1 = Lay<C, F, SD, 1>;
   using L2 = Lay<C, F, SD, 2>;
@@ -133,7 +138,7 @@ __global__ __launch_bounds__(kT) void k_encoder32_fwd(const float* __restrict__ 
   Weights<L0, F> w0;
   Weights<L1, F> w1;
   w0.load(w.W[0]);
-  copy4(x + img * C * L0::PI, ra, C * L0::PI);
+  copy4(x + img * C * L0::PI, ra, C * L0::PI, xsave ? xsave + img * C * L0::PI : nullptr);
   w1.load(w.W[1]);
   w0.store(rw);
   fill_fwd<L0>(tab);
@@ -153,7 +158,7 @@ __global__ __launch_bounds__(kT) void k_encoder32_fwd(const float* __restrict__ 
   __syncthreads();
   layer_fwd<L2, F>(ra, rw, tab, w.b[2], rb);
   __syncthreads();
-  copy4(rb, h.h[2] + img * F * L2::P, F * L2::P);
+  copy4(rb, h.h[2] + img * F * L2::P, F * L2::P, feat2 ? feat2 + img * F * L2::P : nullptr);
 }
 
 // ---------------------------------------------------------------- backward
@@ -323,13 +328,13 @@ __global__ __launch_bounds__(kT) void k_encoder32_bwd(const float* __restrict__ 
 bool encoder32_ok(int C, int F, int n_conv, int side) { return C == 9 && F == 32 && n_conv == 3 && side == 32; }
 
 int encoder32_fwd(const float* x, int n, const float* const* W, const float* const* b, float* const* h,
-                  hipStream_t st) {
+                  float* xsave, float* feat2, hipStream_t st) {
   // copies take 16 bytes at a time; a caller's own image or feature buffer (the form
   // without a workspace) may be aligned to 4
   if (((uintptr_t)x | (uintptr_t)h[2]) % 16 != 0) return kNotApplicable;
   if (n <= 0) return SQ_OK;
   k_encoder32_fwd<9, 32, 32><<<n, kT, 0, st>>>(x, Ptrs{{W[0], W[1], W[2]}, {b[0], b[1], b[2]}},
-                                               Acts{{h[0], h[1], h[2]}});
+                                               Acts{{h[0], h[1], h[2]}}, xsave, feat2);
   return launch_status("encoder32_fwd");
 }
 

@@ -119,9 +119,25 @@ int encoder_prepare(const Net& net, int bf16, const float* ep, const Layout& L, 
 }
 
 int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, const float* x, int n,
-                    const EncBufs& e, hipStream_t st, bool prepared) {
+                    const EncBufs& e, hipStream_t st, bool prepared, float* x_save, float* feat2) {
   const sq_dims& d = net.d;
-  if (encoder_fused(net, bf16, e)) {
+  const bool fused = encoder_fused(net, bf16, e), e32 = !fused && !bf16 && encoder32_ok(d.C, d.F, d.n_conv, net.side);
+  auto al16 = [](const void* p) { return (uintptr_t)p % 16 == 0; };
+  // copies that the launch below does not make (an image buffer that the features are
+  // written over is copied first)
+  const bool over = x_save && feat2 && (uintptr_t)feat2 < (uintptr_t)(x + (size_t)n * net.img) &&
+                    (uintptr_t)x < (uintptr_t)(feat2 + (size_t)n * net.flat);
+  if (x_save && (over || (!(fused && bf16) && !(e32 && al16(x))))) {
+    SQ_TRY_HIP(hipMemcpyAsync(x_save, x, (size_t)n * net.img * 4, hipMemcpyDeviceToDevice, st));
+    x = x_save;
+    x_save = nullptr;
+  }
+  if (feat2 && !(fused && bf16) && !(e32 && al16(feat2))) {
+    SQ_TRY(encoder_forward(net, bf16, ep, L, x, n, e, st, prepared, x_save));
+    SQ_TRY_HIP(hipMemcpyAsync(feat2, e.h[d.n_conv - 1], (size_t)n * net.flat * 4, hipMemcpyDeviceToDevice, st));
+    return SQ_OK;
+  }
+  if (fused) {
     const float* b[4];
     float* h[4];
     for (int i = 0; i < d.n_conv; ++i) {
@@ -130,16 +146,17 @@ int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, 
     }
     if (!prepared) SQ_TRY(encoder_prepare(net, bf16, ep, L, e, st));
     uint16_t* hh = bf16 ? twin_of(h[d.n_conv - 1], (long long)n * net.flat) : nullptr;
-    return encoder_fused_fwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, e.wprep, b, h, e.enc_part != nullptr, st, hh);
+    return encoder_fused_fwd(bf16, d.C, d.F, d.n_conv, net.side, x, n, e.wprep, b, h, e.enc_part != nullptr, st, hh,
+                             x_save, feat2);
   }
-  if (!bf16 && encoder32_ok(d.C, d.F, d.n_conv, net.side)) {
+  if (e32) {
     const float* W[3];
     const float* b[3];
     for (int i = 0; i < 3; ++i) {
       W[i] = ep + L.conv_W[i];
       b[i] = ep + L.conv_b[i];
     }
-    const int s = encoder32_fwd(x, n, W, b, e.h, st);
+    const int s = encoder32_fwd(x, n, W, b, e.h, x_save, feat2, st);
     if (s != kNotApplicable) return s;
   }
   const float* in = x;

@@ -19,8 +19,11 @@ struct EncBufs {
 void plan_encoder(const Net& net, int n, Bump& b, EncBufs* e, bool with_bwd);
 // prepared: e.wprep already holds the rearranged weights of these parameters
 // (kept current by the optimiser through an EncPrepMap)
+// x_save, feat2 (nullable): x is also copied to x_save (16-byte aligned), the features to
+// feat2 -- by the encoder's own launch where it can
 int encoder_forward(const Net& net, int bf16, const float* ep, const Layout& L, const float* x, int n,
-                    const EncBufs& e, hipStream_t st, bool prepared = false);
+                    const EncBufs& e, hipStream_t st, bool prepared = false, float* x_save = nullptr,
+                    float* feat2 = nullptr);
 // bfloat16: the minibatch draw sa, the squint of its frames into x (2 sa.B images)
 // and the encoder forward in one launch; kNotApplicable when that form does not apply.
 // stored: the frames are the block means a ring stored at insertion

@@ -691,7 +691,7 @@ __global__ __launch_bounds__(NT, SQK <= 1 && SD == 16 ? 3 : 2) void k_encoder_fw
     }
   };
   stage(first);
-  lds_barrier();
+  if constexpr (SQK > 0) lds_barrier();
   for (int img = first; img < a.n; img += stride) {
     const bool save = img < a.nsave, more = img + stride < a.n;
     const long long io = img;
@@ -714,8 +714,10 @@ __global__ __launch_bounds__(NT, SQK <= 1 && SD == 16 ? 3 : 2) void k_encoder_fw
       }
 #pragma unroll
       for (int i = 0; i < L0::CP / 8; ++i) *reinterpret_cast<bf16x8*>(&lx[p * L0::PS + 8 * i]) = px[i];
-      lds_barrier();
     }
+    // the input is complete, and everybody has read the last image's features, whose
+    // place the first layer takes
+    lds_barrier();
     conv_fwd_layer_b<C, F, 0, SD, false, NT>(lx, la0, save ? a.h[0] + io * F * L0::P : nullptr, w0);
     lds_barrier();
     if constexpr (NC > 2) {

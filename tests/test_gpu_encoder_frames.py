@@ -4,6 +4,7 @@ that are not 16-byte aligned take the latter."""
 import pytest
 import torch
 
+from oracle import layout as olayout
 from paper_2602_21203_amd import synthetic
 from tests import helpers as H
 
@@ -63,3 +64,19 @@ def test_update_equals_separate_launches(B, stored):
         ag.close()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("name,n,prec", [("full", 1300, 1), ("full32", 600, 1), ("tiny", 1300, 1)])
+def test_many_images_equal_few(name, n, prec):
+    """Workgroups that take several images in turn give each the features that it has
+    when every workgroup takes one."""
+    print(f"encoder many images {name} n={n}", flush=True)
+    cfg = H.cfg(name)
+    end = olayout.blocks(olayout.dims(**cfg))["enc"][1]
+    p = torch.tensor(H.params(name)[:end], dtype=torch.float32, device="cuda")
+    side = cfg["H"] // cfg["k"]
+    x = torch.rand((n, cfg["C"], side, side), generator=torch.Generator().manual_seed(n)).cuda() - 0.5
+    parts = torch.cat([api.encoder_fwd(cfg, prec, p, c.contiguous())[0] for c in x.split(200)])
+    for _ in range(3):
+        assert torch.equal(api.encoder_fwd(cfg, prec, p, x)[0], parts)
+        assert torch.equal(api.encoder_fwd_noalloc(cfg, prec, p, x[:300]), parts[:300])

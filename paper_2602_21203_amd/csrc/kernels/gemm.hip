@@ -1226,17 +1226,18 @@ static StMat stmat(const OutArg& c) {
   return StMat{c.p, c.ld, c.sz, c.bias, c.bias_sz, c.accumulate, c.relu, c.bias_alt, c.bias_zalt};
 }
 
-// Whether a product takes the 64 x 64 tile: enough of those tiles, FP32 operands at
-// least one a compute unit, bfloat16 copies (whose 32 x 32 form reads half the bytes
-// and keeps its lead longer) about two.  Measured, 32 x 32 -> 64 x 64 tile, us:
-//   FP32 operands, FP32 / bfloat16 mode   copies
-//   128 tiles (2 x 512^3)           10.9 -> 16.3   6.8 -> 9.4     6.0 -> 8.5
-//   256 tiles (4 x 512^3)           19.4 -> 17.3  11.1 -> 9.9     8.3 -> 8.9
-//   512 tiles (2 x 2048x512x512)    36.4 -> 26.9  20.7 -> 13.1   14.1 -> 11.8
-//   1024 tiles (4 x 2048x512x512)   70.2 -> 48.9  39.4 -> 20.7   24.1 -> 17.8
+// Whether a product takes the 64 x 64 tile: enough of those tiles, one a compute unit
+// for FP32 arithmetic, most of two in bfloat16 (whose products are shorter and keep the
+// 32 x 32 tile's lead longer).  Measured, 32 x 32 -> 64 x 64 tile, us:
+//                                        FP32        bfloat16 on FP32 operands   copies
+//    128 tiles (2 x 512^3)          11.3 -> 16.1      6.5 -> 9.3           5.9 -> 8.3
+//    256 tiles (4 x 512^3)          19.7 -> 16.7      8.6 -> 9.6           7.6 -> 8.5
+//    384 tiles (6 x 512^3)          24.3 -> 23.9     11.4 -> 11.7         10.0 -> 10.5
+//    512 tiles (2 x 2048x512x512)   31.7 -> 24.4     13.6 -> 12.1         11.9 -> 10.9
+//   1024 tiles (4 x 2048x512x512)   56.4 -> 44.0     24.1 -> 18.6         19.8 -> 15.9
 // A k-concatenated operand needs whole stages on both sides, and the byte offsets of
 // an operand's rows inside a batch 32 bits.
-constexpr long long kBigMinF = 256, kBigMinH = 384;
+constexpr long long kBigMinF = 256, kBigMinH = 448;
 
 static long long big_tiles(int M, int N, int batch) {
   return (long long)cdiv(M, kBigTile) * cdiv(N, kBigTile) * batch;
@@ -1250,8 +1251,8 @@ static bool big_rows_ok(const HMat& m, int rows, bool t) {
   const long long lim = 1LL << 30;   // elements
   return (t ? kBigK : (long long)rows) * m.ld < lim && (m.kalt == kNoAlt || m.kalt % kBigK == 0);
 }
-static bool big_ok_f(int M, int N, int K, int batch, const MatArg& A, const MatArg& B) {
-  return big_tiles(M, N, batch) >= kBigMinF && big_rows_ok(A, M, K) && big_rows_ok(B, N, K);
+static bool big_ok_f(int bf16, int M, int N, int K, int batch, const MatArg& A, const MatArg& B) {
+  return big_tiles(M, N, batch) >= (bf16 ? kBigMinH : kBigMinF) && big_rows_ok(A, M, K) && big_rows_ok(B, N, K);
 }
 static bool big_ok_h(int M, int N, int batch, const HMat& a, bool ta, const HMat& b, bool tb) {
   return big_tiles(M, N, batch) >= kBigMinH && big_rows_ok(a, M, ta) && big_rows_ok(b, N, tb);
@@ -1466,7 +1467,7 @@ int gemm(int bf16, int M, int N, int K, int batch, MatArg A, MatArg B, OutArg C,
     if (h != kNotApplicable) return h;
   }
   if (!fp32) return refuse_dropped("gemm");
-  if (want_splits(M, N, K, batch, scratch, scratch_floats) == 1 && big_ok_f(M, N, K, batch, A, B))
+  if (want_splits(M, N, K, batch, scratch, scratch_floats) == 1 && big_ok_f(bf16, M, N, K, batch, A, B))
     return bf16 ? run_big<true>(M, N, K, batch, A, B, out, st) : run_big<false>(M, N, K, batch, A, B, out, st);
   if (bf16) {
     if (va && vb) return run_r<true, 1, 1>(M, N, K, batch, A, B, out, scratch, scratch_floats, st);
@@ -1659,8 +1660,9 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     }
   }
   if (!fp32_ok(p0.A) || !fp32_ok(p0.B) || !fp32_ok(p1.A) || !fp32_ok(p1.B)) return refuse_dropped("gemm_pair");
+  const long long big_min = bf16 ? kBigMinH : kBigMinF;
   const bool rows0 = big_rows_ok(p0.A, p0.M, p0.K) && big_rows_ok(p0.B, p0.N, p0.K);
-  if (!fwd_kinds && rows0 && b0 >= kBigMinF) {
+  if (!fwd_kinds && rows0 && b0 >= big_min) {
     q0.gx = cdiv(p0.M, kBigTile);
     q0.gy = cdiv(p0.N, kBigTile);
     const int ka = big_kind(p0.A), kb = big_kind(p0.B), n = t1 + (int)b0;
@@ -1678,7 +1680,7 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     q0.gy = cdiv(p0.N, kTile);
   }
   if (fwd_kinds && rows0 && big_rows_ok(p1.A, p1.M, p1.K) && big_rows_ok(p1.B, p1.N, p1.K) &&
-      b0 + b1 >= kBigMinF) {
+      b0 + b1 >= big_min) {
     q0.gx = cdiv(p0.M, kBigTile);
     q0.gy = cdiv(p0.N, kBigTile);
     q1.gx = cdiv(p1.M, kBigTile);

@@ -11,7 +11,7 @@ if torch.cuda.is_available():
     from paper_2602_21203_amd import api
 
 # rows, columns off the tile, batch: (Z ceil(M / 64) ceil(N / 64) tiles: 672, at least the
-# 384 from which both forms of operands take the 64 x 64 tile)
+# 448 from which both forms of operands take the 64 x 64 tile)
 Z, M, N = 16, 390, 333
 STEP = 130   # rows of a block: at most 16 x 3 x 6 = 288 tiles; two batches of it 36
 

@@ -266,7 +266,10 @@ int adam(float* p, const float* g, float* m, float* v, long long n, const sq_hpa
       seg_blocks += (gs->s[i].H + 63) / 64;
     }
   }
-  const AdamArgs A{p, g, m, v, n, hp->lr, hp->beta1, hp->beta2, hp->adam_eps, step, ema_target, ema_begin, hp->rho,
+  // an average over no parameters: its target is not read (adam_load reads its first element for
+  // the parameters below ema_begin)
+  float* const ema = ema_begin < n ? ema_target : nullptr;
+  const AdamArgs A{p, g, m, v, n, hp->lr, hp->beta1, hp->beta2, hp->adam_eps, step, ema, ema_begin, hp->rho,
                    shadow, ep ? *ep : EncPrepMap{}};
   const FinishJob nofj{};
   const unsigned grid = (unsigned)(blocks + seg_blocks + (aj || fj ? 1 : 0));

@@ -1,0 +1,50 @@
+// What the launchers hand to the kernels, checked without a GPU: hipLaunchKernel is
+// replaced by a recorder.  Linked against the library's objects by
+// test_cpu_launch_args.py; each check is named on the command line and exits 0.
+#include <stdint.h>
+#include <stdio.h>
+#include <string.h>
+
+#include "common.h"
+
+using namespace sq;
+
+// The replaced launch looks for one pointer in the first bytes of the kernel's first
+// argument (a struct larger than that).
+static const void* g_wanted = nullptr;
+static int g_launches = 0, g_found = 0;
+
+extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
+  ++g_launches;
+  for (size_t o = 0; o + sizeof(void*) <= 96; o += sizeof(void*))
+    if (g_wanted && memcmp((const char*)args[0] + o, &g_wanted, sizeof(void*)) == 0) ++g_found;
+  return hipSuccess;
+}
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* st) {
+  *g = *b = dim3(1);
+  *n = 0;
+  *st = nullptr;
+  return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+
+// whether the optimiser's kernel is handed the target of an average that starts at `begin` of 8
+static bool ema_handed(long long begin) {
+  static float p[8], g[8], m[8], v[8], target[1];
+  int step = 0;
+  sq_hparams hp{};
+  g_wanted = target;
+  g_launches = g_found = 0;
+  const int s = adam(p, g, m, v, 8, &hp, &step, target, begin, nullptr, nullptr, nullptr);
+  printf("status %d, %d launches, pointer handed %d times\n", s, g_launches, g_found);
+  return s == SQ_OK && g_launches == 1 && g_found == 1;
+}
+
+int main(int argc, char** argv) {
+  const char* what = argc > 1 ? argv[1] : "";
+  if (!strcmp(what, "adam_average")) return ema_handed(0) && ema_handed(7) ? 0 : 1;
+  if (!strcmp(what, "adam_empty_average")) return !ema_handed(8) ? 0 : 1;
+  printf("unknown check '%s'\n", what);
+  return 2;
+}

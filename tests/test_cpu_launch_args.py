@@ -1,0 +1,29 @@
+"""What the launchers hand to the kernels, on a machine without a GPU: launch_args.cpp,
+linked against the library's objects, replaces the kernel launch by a recorder."""
+import glob
+import os
+import subprocess
+
+import pytest
+
+from paper_2602_21203_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    objs = sorted(glob.glob(os.path.join(build.OBJ, "*.o")))
+    if len(objs) != len(build.SOURCES):
+        pytest.skip("the library's objects are not here (built with it)")
+    out = str(tmp_path_factory.mktemp("launch") / "launch_args")
+    subprocess.run([build.hipcc(), "-O1", "-std=c++17", f"--offload-arch={build.ARCH}", "-I",
+                    os.path.join(build.ROOT, "include"), "-I", build.CSRC, "-x", "hip",
+                    os.path.join(HERE, "launch_args.cpp"), "-x", "none", *objs, "-o", out], check=True)
+    return out
+
+
+# the target is a pointer that the kernel may read only where the average has elements
+@pytest.mark.parametrize("check", ["adam_average", "adam_empty_average"])
+def test_launch_arguments(program, check):
+    assert subprocess.run([program, check], timeout=60).returncode == 0

@@ -70,6 +70,7 @@ struct Slot {
   float* prop_stage = nullptr;
   float* act_stage = nullptr;
   std::vector<Req> batch;
+  int rows = 0;            // of the batch
   bool busy = false;
   bool finished = false;   // set by the stream's host function when the batch is done
   size_t bytes = 0;
@@ -114,7 +115,11 @@ static void batch_done(void* arg) {
   s->cv.notify_one();
 }
 
-static int launch_batch(sq_server* s, Slot& sl) {
+// A batch is enqueued in two parts: its start, inputs and encoder; then the policy, the
+// outputs and its end.  Of batches admitted together the first parts are all enqueued
+// before any second one, so they run at once on the device also where a batch takes
+// less time there than its enqueueing here.
+static int launch_inputs(sq_server* s, Slot& sl) {
   const sq_dims& d = s->net.d;
   const int cap = s->max_batch;
   Tables h = carve_tables(sl.htab, cap);
@@ -129,8 +134,8 @@ static int launch_batch(sq_server* s, Slot& sl) {
       h.rows[r] = i;
       h.sample[r] = q.sample;
     }
-  const int n = r;
-  Tables t = carve_tables(sl.dtab, cap);
+  const int n = sl.rows = r;
+  const Tables t = carve_tables(sl.dtab, cap);
   hipStream_t st = sl.st;
   SQ_TRY_HIP(hipEventRecord(sl.ev0, st));
   SQ_TRY_HIP(hipMemcpyAsync(sl.dtab, sl.htab, tables_bytes(cap), hipMemcpyHostToDevice, st));
@@ -140,7 +145,14 @@ static int launch_batch(sq_server* s, Slot& sl) {
     SQ_TRY(encoder_forward(s->net, bf, s->params, s->L, sl.w.x, n, sl.w.e, st));
   }
   if (d.proprio > 0) SQ_TRY(gather_rows((const float* const*)t.prop, d.proprio, n, sl.prop_stage, st));
-  SQ_TRY(act_noise_rows(s->hp.seed, t.ids, t.rows, t.sample, n, d.action, sl.w.noise, st));
+  return act_noise_rows(s->hp.seed, t.ids, t.rows, t.sample, n, d.action, sl.w.noise, st);
+}
+
+static int launch_policy(sq_server* s, Slot& sl) {
+  const sq_dims& d = s->net.d;
+  const int n = sl.rows, bf = s->hp.prec == SQ_BF16;
+  const Tables t = carve_tables(sl.dtab, s->max_batch);
+  hipStream_t st = sl.st;
   // state-based: the gathered states are the features
   const float* feat = d.n_conv > 0 ? sl.w.e.h[d.n_conv - 1] : sl.prop_stage;
   SQ_TRY(actor_forward(s->net, bf, s->params + s->L.actor_begin, agent_pack(s->agent), s->L, feat,
@@ -234,13 +246,15 @@ static void scheduler(sq_server* s) {
       lk.unlock();
       int err = SQ_OK;
       char msg[256] = {0};
-      for (Slot* sl : launch)
-        if (launch_batch(s, *sl) != SQ_OK) {
-          err = SQ_EDEVICE;
-          snprintf(msg, sizeof(msg), "%s", sq_last_error());
-          (void)hipStreamSynchronize(sl->st);
-          batch_done(sl);   // nothing more will complete on this slot's stream
-        }
+      for (const auto part : {launch_inputs, launch_policy})
+        for (Slot*& sl : launch)
+          if (sl && part(s, *sl) != SQ_OK) {
+            err = SQ_EDEVICE;
+            snprintf(msg, sizeof(msg), "%s", sq_last_error());
+            (void)hipStreamSynchronize(sl->st);
+            batch_done(sl);   // nothing more will complete on this slot's stream
+            sl = nullptr;
+          }
       const double t = now_s();
       for (const Req& r : fire)
         if (r.cb) r.cb(r.id, t, r.user);
@@ -314,11 +328,16 @@ int sq_server_create(sq_agent* agent, size_t mem_budget, int max_batch_obs, int 
     sl.act_stage = c.take<float>((size_t)max_batch_obs * d.action);
     sl.dtab = c.take<char>(tables_bytes(max_batch_obs));
   }
-  for (Slot& sl : s->slots) sl.srv = s;
-  if (hipEventCreate(&s->ref) != hipSuccess || hipEventRecord(s->ref, s->slots[0].st) != hipSuccess ||
+  // (every stream is used once here, so that no batch waits for a stream's first use)
+  bool used = true;
+  for (Slot& sl : s->slots) {
+    sl.srv = s;
+    used = used && hipEventRecord(sl.ev0, sl.st) == hipSuccess && hipEventSynchronize(sl.ev0) == hipSuccess;
+  }
+  if (!used || hipEventCreate(&s->ref) != hipSuccess || hipEventRecord(s->ref, s->slots[0].st) != hipSuccess ||
       hipEventSynchronize(s->ref) != hipSuccess) {
     free_server(s);
-    set_error("creating the server's reference event failed");
+    set_error("using the serving slots' streams or creating the reference event failed");
     return SQ_EDEVICE;
   }
   s->th = std::thread(scheduler, s);

@@ -743,7 +743,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_r(RMat fa, RMat fb, ST st, St
 // Every column tile repeats that, which costs less than a launch as long as the rows are
 // few (kLnGemmRows).
 struct LnRows {
-  const float* pre; long long ld_pre; const float* g; const float* beta; int H, act_tanh;
+  const float* pre; long long ld_pre; const float* g; const float* beta; int act_tanh;
   const float* e1; long long ld_e1; int w1;
 };
 
@@ -1494,7 +1494,13 @@ bool gemm_ln_ok(const LnIn& x, int n) {
 
 template <class ST>
 static int launch_gemm_ln(int bf16, int n, int N, const LnIn& x, const MatArg& W, const ST& st, hipStream_t stream) {
-  const LnRows j{x.pre, x.ld_pre, x.g, x.beta, x.H, x.act_tanh, x.e1, x.ld_e1, x.w1};
+  if (!gemm_ln_ok(x, n) || W.lk != 1) {
+    set_error("gemm_ln: %d rows of %d + %d columns: needs at most %d rows of 256 or 512 (16-byte aligned) and "
+              "k-contiguous weights", n, x.H, x.w1, kLnGemmRows);
+    return SQ_EINVAL;
+  }
+  if (!fp32_ok(W) || fp32_dropped(x.pre) || fp32_dropped(x.e1)) return refuse_dropped("gemm_ln");
+  const LnRows j{x.pre, x.ld_pre, x.g, x.beta, x.act_tanh, x.e1, x.ld_e1, x.w1};
   const dim3 grid(cdiv(n, kTile), cdiv(N, kTile));
   const RMat w = rmat(W);
   const int K = x.H + x.w1;
@@ -1511,6 +1517,10 @@ int gemm_ln(int bf16, int n, int N, const LnIn& x, MatArg W, OutArg C, hipStream
 
 int gemm_ln_tanh_gauss(int bf16, int n, int A, const LnIn& x, MatArg W, const float* bias, const float* eps, float lo,
                        float hi, float* action, float* logp, float* save, float* head, hipStream_t st) {
+  if (2 * A > kTile) {
+    set_error("gemm_ln_tanh_gauss: %d head columns, more than a tile's %d", 2 * A, kTile);
+    return SQ_EINVAL;
+  }
   const StTanhGauss tg{bias, eps, lo, hi, action, logp, save, head, A, nullptr, 0, 0, nullptr};
   return launch_gemm_ln(bf16, n, 2 * A, x, W, tg, st);
 }

@@ -41,10 +41,50 @@ static bool ema_handed(long long begin) {
   return s == SQ_OK && g_launches == 1 && g_found == 1;
 }
 
+// the few-row product that normalises its own input: 4 rows of H, weights [N, H]
+struct LnCall {
+  int n = 4, H = 256, A = 6;
+  long long lk = 1;
+  // launched (true) or refused without a launch
+  bool launches(bool head) const {
+    g_wanted = nullptr;
+    g_launches = 0;
+    const LnIn x{pre(), H, pre(), pre(), H, 1, nullptr, 0, 0};
+    const MatArg W{weights(), H, lk, 0};
+    float* out = pre();
+    const int s = head ? gemm_ln_tanh_gauss(0, n, A, x, W, nullptr, nullptr, -5.f, 2.f, out, nullptr, nullptr, out, nullptr)
+                       : gemm_ln(0, n, 2 * A, x, W, OutArg{out, 2 * A, 0, nullptr, 0, 0, 0}, nullptr);
+    if (s != (g_launches ? SQ_OK : SQ_EINVAL) || g_launches > 1) printf("status %d, %d launches\n", s, g_launches);
+    return s == SQ_OK && g_launches == 1;
+  }
+  static float* pre() { static float b[64 * 512] __attribute__((aligned(16))); return b; }
+  static float* weights() { static float b[64 * 512] __attribute__((aligned(16))); return b; }
+};
+
+static bool ln_dropped(const float* buffer) {
+  int owner = 0;
+  fp32_drop_register(&owner, buffer, 64 * 512);
+  const bool refused = !LnCall().launches(false) && !LnCall().launches(true);
+  twin_unregister(&owner);
+  return refused && LnCall().launches(false) && LnCall().launches(true);
+}
+
+static bool ln_form_refused(LnCall c) { return !c.launches(false) && !c.launches(true); }
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "adam_average")) return ema_handed(0) && ema_handed(7) ? 0 : 1;
   if (!strcmp(what, "adam_empty_average")) return !ema_handed(8) ? 0 : 1;
+  if (!strcmp(what, "ln_dropped_weights")) return ln_dropped(LnCall::weights()) ? 0 : 1;
+  if (!strcmp(what, "ln_dropped_input")) return ln_dropped(LnCall::pre()) ? 0 : 1;
+  if (!strcmp(what, "ln_forms")) {
+    LnCall rows, width, strided, wide;
+    rows.n = 17;
+    width.H = 320;
+    strided.lk = 2;
+    wide.A = 17;   // more head columns than one tile
+    return ln_form_refused(rows) && ln_form_refused(width) && ln_form_refused(strided) && !wide.launches(true) ? 0 : 1;
+  }
   printf("unknown check '%s'\n", what);
   return 2;
 }

@@ -23,7 +23,10 @@ def program(tmp_path_factory):
     return out
 
 
-# the target is a pointer that the kernel may read only where the average has elements
-@pytest.mark.parametrize("check", ["adam_average", "adam_empty_average"])
+# adam: the target is a pointer that the kernel may read only where the average has elements.
+# ln: the products that normalise their own input refuse buffers that keep no FP32 values,
+# and the forms that they are not built for.
+@pytest.mark.parametrize("check", ["adam_average", "adam_empty_average", "ln_dropped_weights", "ln_dropped_input",
+                                   "ln_forms"])
 def test_launch_arguments(program, check):
     assert subprocess.run([program, check], timeout=60).returncode == 0

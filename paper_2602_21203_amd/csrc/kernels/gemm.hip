@@ -1226,18 +1226,29 @@ static StMat stmat(const OutArg& c) {
   return StMat{c.p, c.ld, c.sz, c.bias, c.bias_sz, c.accumulate, c.relu, c.bias_alt, c.bias_zalt};
 }
 
-// Whether a product takes the 64 x 64 tile: enough of those tiles, one a compute unit
-// for FP32 arithmetic, most of two in bfloat16 (whose products are shorter and keep the
-// 32 x 32 tile's lead longer).  Measured, 32 x 32 -> 64 x 64 tile, us:
+// Whether a product takes the 64 x 64 tile: enough of those tiles for the chip's 256
+// compute units.  Measured, 32 x 32 -> 64 x 64 tile, us:
 //                                        FP32        bfloat16 on FP32 operands   copies
 //    128 tiles (2 x 512^3)          11.3 -> 16.1      6.5 -> 9.3           5.9 -> 8.3
 //    256 tiles (4 x 512^3)          19.7 -> 16.7      8.6 -> 9.6           7.6 -> 8.5
 //    384 tiles (6 x 512^3)          24.3 -> 23.9     11.4 -> 11.7         10.0 -> 10.5
 //    512 tiles (2 x 2048x512x512)   31.7 -> 24.4     13.6 -> 12.1         11.9 -> 10.9
 //   1024 tiles (4 x 2048x512x512)   56.4 -> 44.0     24.1 -> 18.6         19.8 -> 15.9
+// and how many times faster the 64 x 64 tile is over the contraction (2 x M x 512 x K, at
+// K = 128, 512, 1024; both operands k-contiguous | B k-strided | both):
+//   FP32  256 tiles  1.14 1.21 1.26 | 0.99 1.21 1.25 | 0.91 1.11 1.17
+//         272        0.90 0.89 0.95 | 0.83 0.79 0.81 | 0.74 0.78 0.83
+//         352        1.02 0.99 1.00 | 0.93 0.92 0.97 | 0.83 0.91 0.99
+//         416        1.10 1.11 1.15 | 1.02 1.04 1.11 | 0.93 1.01 1.14
+//         512        1.29 1.32 1.35 | 1.15 1.24 1.33 | 1.05 1.21 1.35
+//   bfloat16 on FP32 operands, copies, 448 to 1,088 tiles: 1.00 to 1.39, 1.00 to 1.58 (both
+//   k-strided on FP32 operands 0.94 at the least, at 544 and 576 tiles)
+// So from 448 tiles in bfloat16, 352 (k-contiguous operands) or 416 in FP32; and in FP32
+// (a k-strided A with more than 256 k) also at exactly one tile a compute unit, where the 32 x
+// 32 tile has four workgroups on each for the three that fit: a few more tiles double the launch.
 // A k-concatenated operand needs whole stages on both sides, and the byte offsets of
 // an operand's rows inside a batch 32 bits.
-constexpr long long kBigMinF = 256, kBigMinH = 448;
+constexpr long long kBigMinH = 448, kBigMinF = 416, kBigMinRowsF = 352, kBigOneF = 256;
 
 static long long big_tiles(int M, int N, int batch) {
   return (long long)cdiv(M, kBigTile) * cdiv(N, kBigTile) * batch;
@@ -1251,8 +1262,13 @@ static bool big_rows_ok(const HMat& m, int rows, bool t) {
   const long long lim = 1LL << 30;   // elements
   return (t ? kBigK : (long long)rows) * m.ld < lim && (m.kalt == kNoAlt || m.kalt % kBigK == 0);
 }
+// krows_a, krows_b: the operand is k-contiguous
+static bool big_fills(int bf16, long long tiles, int K, bool krows_a, bool krows_b) {
+  if (bf16) return tiles >= kBigMinH;
+  return tiles >= (krows_a && krows_b ? kBigMinRowsF : kBigMinF) || (tiles == kBigOneF && (krows_a || K > 256));
+}
 static bool big_ok_f(int bf16, int M, int N, int K, int batch, const MatArg& A, const MatArg& B) {
-  return big_tiles(M, N, batch) >= (bf16 ? kBigMinH : kBigMinF) && big_rows_ok(A, M, K) && big_rows_ok(B, N, K);
+  return big_fills(bf16, big_tiles(M, N, batch), K, krows(A), krows(B)) && big_rows_ok(A, M, K) && big_rows_ok(B, N, K);
 }
 static bool big_ok_h(int M, int N, int batch, const HMat& a, bool ta, const HMat& b, bool tb) {
   return big_tiles(M, N, batch) >= kBigMinH && big_rows_ok(a, M, ta) && big_rows_ok(b, N, tb);
@@ -1670,7 +1686,10 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     }
   }
   if (!fp32_ok(p0.A) || !fp32_ok(p0.B) || !fp32_ok(p1.A) || !fp32_ok(p1.B)) return refuse_dropped("gemm_pair");
-  const long long big_min = bf16 ? kBigMinH : kBigMinF;
+  // in FP32 from one 64 x 64 tile a compute unit on: the other problem's workgroups fill the
+  // rest of a second round (critic of 1,100 rows, 288 tiles, forward and backward: 214.0 us,
+  // this product on 32 x 32 tiles 222.8)
+  const long long big_min = bf16 ? kBigMinH : kBigOneF;
   const bool rows0 = big_rows_ok(p0.A, p0.M, p0.K) && big_rows_ok(p0.B, p0.N, p0.K);
   if (!fwd_kinds && rows0 && b0 >= big_min) {
     q0.gx = cdiv(p0.M, kBigTile);
@@ -1690,7 +1709,7 @@ int gemm_pair(int bf16, const GemmProb& p0, const GemmProb& p1, float* scratch, 
     q0.gy = cdiv(p0.N, kTile);
   }
   if (fwd_kinds && rows0 && big_rows_ok(p1.A, p1.M, p1.K) && big_rows_ok(p1.B, p1.N, p1.K) &&
-      b0 + b1 >= big_min) {
+      big_fills(bf16, b0 + b1, p0.K, true, true)) {
     q0.gx = cdiv(p0.M, kBigTile);
     q0.gy = cdiv(p0.N, kBigTile);
     q1.gx = cdiv(p1.M, kBigTile);

@@ -13,6 +13,7 @@ using namespace sq;
 // argument (a struct larger than that).
 static const void* g_wanted = nullptr;
 static int g_launches = 0, g_found = 0;
+static dim3 g_grid;   // of the last launch
 
 extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
   ++g_launches;
@@ -20,7 +21,10 @@ extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size
     if (g_wanted && memcmp((const char*)args[0] + o, &g_wanted, sizeof(void*)) == 0) ++g_found;
   return hipSuccess;
 }
-extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3, size_t, hipStream_t) {
+  g_grid = grid;
+  return hipSuccess;
+}
 extern "C" hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, hipStream_t* st) {
   *g = *b = dim3(1);
   *n = 0;
@@ -71,6 +75,33 @@ static bool ln_dropped(const float* buffer) {
 
 static bool ln_form_refused(LnCall c) { return !c.launches(false) && !c.launches(true); }
 
+// the tile (64 or 32) that a product of 2 x 64 t x 512 x 512 runs on: 16 t tiles of 64 x 64
+static int tile(int bf16, int t, bool a_rows, bool b_rows) {
+  float* p = LnCall::pre();   // not read
+  const int M = 64 * t, N = 512, K = 512;
+  const MatArg A{p, a_rows ? K : 1, a_rows ? 1 : M, (long long)M * K};
+  const MatArg B{p, b_rows ? K : 1, b_rows ? 1 : N, (long long)N * K};
+  g_launches = 0;
+  const int s = gemm(bf16, M, N, K, 2, A, B, OutArg{p, N, (long long)M * N, nullptr, 0, 0, 0}, nullptr, 0, nullptr);
+  if (s != SQ_OK || g_launches != 1 || (int)g_grid.z != 2) return 0;
+  return M / (int)g_grid.x;
+}
+
+static bool tile_lines() {
+  // {bfloat16, A's and B's rows k-contiguous, t, tile} on both sides of every line
+  const int want[][5] = {{0, 1, 1, 15, 32}, {0, 1, 1, 16, 64}, {0, 1, 1, 17, 32}, {0, 1, 1, 21, 32}, {0, 1, 1, 22, 64},
+                         {0, 1, 0, 16, 64}, {0, 1, 0, 17, 32}, {0, 1, 0, 25, 32}, {0, 1, 0, 26, 64},
+                         {0, 0, 0, 16, 64}, {0, 0, 0, 17, 32}, {0, 0, 0, 25, 32}, {0, 0, 0, 26, 64},
+                         {1, 1, 1, 16, 32}, {1, 1, 1, 27, 32}, {1, 1, 1, 28, 64}, {1, 0, 0, 27, 32}, {1, 0, 0, 28, 64}};
+  bool ok = true;
+  for (const auto& w : want) {
+    const int got = tile(w[0], w[3], w[1], w[2]);
+    if (got != w[4]) printf("bf16 %d rows %d %d, %d tiles: %d\n", w[0], w[1], w[2], 16 * w[3], got);
+    ok = ok && got == w[4];
+  }
+  return ok;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "adam_average")) return ema_handed(0) && ema_handed(7) ? 0 : 1;
@@ -85,6 +116,7 @@ int main(int argc, char** argv) {
     wide.A = 17;   // more head columns than one tile
     return ln_form_refused(rows) && ln_form_refused(width) && ln_form_refused(strided) && !wide.launches(true) ? 0 : 1;
   }
+  if (!strcmp(what, "tile_lines")) return tile_lines() ? 0 : 1;
   printf("unknown check '%s'\n", what);
   return 2;
 }

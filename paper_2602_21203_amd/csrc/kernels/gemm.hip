@@ -408,11 +408,11 @@ __global__ __launch_bounds__(kThreads) void k_gemm(FA fa, FB fb, ST st, StPart s
 // times more.  Other operands (k strided, rows contiguous) are read in fragment
 // order directly, which is already coalesced across li.
 //
-// Two chunks are in flight, one register buffer each: the next loads while the current
-// one is multiplied.  (Buffers of two chunks each held a compute unit to two workgroups by
-// their registers and LDS, where three fit now: actor of 1,000 rows in FP32, its largest
-// pair 27.4 -> 21.2 us, critic of 512 rows in bfloat16 103.0 -> 99.7 us of kernels.)  The four partial tiles are summed through LDS in a
-// fixed order at the end.  bfloat16 operands are rounded to nearest even
+// Two register groups of G chunks are in flight: the next loads while the current one is
+// multiplied.  Groups of one chunk let a compute unit hold three workgroups, of two, by
+// their registers and LDS, two (actor of 1,000 rows in FP32, its largest pair 21.2 against
+// 27.4 us; critic of 512 rows in bfloat16 99.7 against 103.0 us of kernels): two_chunks()
+// says which.  The four partial tiles are summed through LDS in a fixed order at the end.  bfloat16 operands are rounded to nearest even
 // (v_cvt_pk_bf16_f32) on the way to LDS or to the fragment.
 struct RMat {
   const float* p; long long lr, lk, sz;
@@ -429,13 +429,12 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // at any f
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRKC = 32;   // k per chunk
-constexpr int kRG = 1;     // chunks per register group
 
 template <bool BF16> struct RLds {
   using T = typename std::conditional<BF16, __bf16, float>::type;
   static constexpr int LDT = BF16 ? 40 : 36;              // row stride of a transposition tile (elements)
   static constexpr int TILE = 32 * LDT;                   // one operand's 32 x 32 chunk
-  static constexpr int WAVE = 2 * kRG * TILE;             // two operands for each chunk of a group
+  static constexpr int WAVE = 2 * TILE;                   // two operands for each chunk of a group
 };
 
 // An operand whose rows the workgroup has normalised itself (V = 2 below): its 32 rows of
@@ -620,24 +619,24 @@ __device__ __forceinline__ void tile_out(const v4f (&acc)[2][2], const ST& st, c
   }
 }
 
-template <bool BF16, int AV, int BV>
+template <bool BF16, int AV, int BV, int G = 1>
 constexpr int gemm_lds_bytes() {
   using LL = RLds<BF16>;
   constexpr int RED_BYTES = 4 * kTile * (kTile + 1) * 4;
-  constexpr int TILE_BYTES = (AV || BV) ? 4 * LL::WAVE * (int)sizeof(typename LL::T) : 0;
+  constexpr int TILE_BYTES = (AV || BV) ? 4 * G * LL::WAVE * (int)sizeof(typename LL::T) : 0;
   return TILE_BYTES > RED_BYTES ? TILE_BYTES : RED_BYTES;
 }
 
 // one 32 x 32 output tile (bx, by) of batch / split index bz; AV = 2: before() fills the
 // A panel, once B's first chunks have been requested
 struct NoPanel { __device__ __forceinline__ void operator()() const {} };
-template <bool BF16, int AV, int BV, class ST, bool SPLIT, class BEFORE = NoPanel>
+template <bool BF16, int AV, int BV, class ST, bool SPLIT, int G = 1, class BEFORE = NoPanel>
 __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const ST& st, const StPart& sp, int M,
                                           int N, int K, int kchunk, int bx, int by, int bz, char* lds,
                                           const BEFORE& before = {}, const typename RLds<BF16>::T* panel = nullptr) {
   using LL = RLds<BF16>;
   using T = typename LL::T;
-  constexpr int KC = kRKC, G = kRG;
+  constexpr int KC = kRKC;
 
   const int z = bz / (SPLIT ? sp.splits : 1);
   const int split = SPLIT ? bz % sp.splits : 0;
@@ -648,7 +647,7 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
   const int kend = min(K, kbeg + kchunk);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: chunk tests stay scalar
-  T* wt = reinterpret_cast<T*>(lds) + wave * LL::WAVE;   // this wave's tiles: [chunk of the group][operand]
+  T* wt = reinterpret_cast<T*>(lds) + wave * G * LL::WAVE;   // this wave's tiles: [chunk of the group][operand]
   // this wave's k range: a quarter of the workgroup's, in whole chunks
   const int span = kend > kbeg ? kend - kbeg : 0;
   const int per = ((span + 3) / 4 + KC - 1) / KC * KC;
@@ -714,9 +713,17 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
       if (g + 3 < ngf) load(g + 3, 1);
     }
   }
-  // the partial last chunk
-  static_assert(G == 1, "groups cover every whole chunk");
-  const int k0 = wb + ngf * KC;
+  int k0 = wb + ngf * G * KC;
+  // a whole chunk short of a group, then the partial last one
+  if constexpr (G == 2) {
+    if (k0 + KC <= we) {
+      float ta[16], tb[16];
+      rload<AV, true>(oa, ta, m0, M, k0, we, lane);
+      rload<BV, true>(ob, tb, n0, N, k0, we, lane);
+      chunk(ta, tb, k0);
+      k0 += KC;
+    }
+  }
   if (k0 < we) {
     float ta[16], tb[16];
     rload<AV, false>(oa, ta, m0, M, k0, we, lane);
@@ -727,14 +734,15 @@ __device__ __forceinline__ void gemm_tile(const RMat& fa, const RMat& fb, const 
   tile_out<ST, SPLIT>(acc, st, sp, M, N, m0, n0, z, split, wave, lane, lds);
 }
 
-template <bool BF16, int AV, int BV, class ST, bool SPLIT>
+template <bool BF16, int AV, int BV, class ST, bool SPLIT, int G = 1>
 __global__ __launch_bounds__(kThreads) void k_gemm_r(RMat fa, RMat fb, ST st, StPart sp, int M, int N, int K,
                                                      int kchunk) {
-  __shared__ __attribute__((aligned(16))) char lds[gemm_lds_bytes<BF16, AV, BV>()];
+  static_assert(G == 1 || G == 2, "chunks per register group");
+  __shared__ __attribute__((aligned(16))) char lds[gemm_lds_bytes<BF16, AV, BV, G>()];
   int bx, by, bz;
   tile_of(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z, bx, by,
           bz);
-  gemm_tile<BF16, AV, BV, ST, SPLIT>(fa, fb, st, sp, M, N, K, kchunk, bx, by, bz, lds);
+  gemm_tile<BF16, AV, BV, ST, SPLIT, G>(fa, fb, st, sp, M, N, K, kchunk, bx, by, bz, lds);
 }
 
 // A product whose input rows are the LayerNorm + activation of `pre` (and copied
@@ -790,7 +798,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_ln(LnRows ln, RMat fb, ST st,
   const RMat none{nullptr, 0, 0, 0, nullptr, kNoAlt, 1, nullptr, kNoAlt};
   const StPart nosp{nullptr, 0, 0, 1};
   const int m0 = (int)blockIdx.x * kTile;
-  gemm_tile<BF16, 2, 1, ST, false>(none, fb, st, nosp, M, N, K, K, blockIdx.x, blockIdx.y, 0, lds,
+  gemm_tile<BF16, 2, 1, ST, false, 1>(none, fb, st, nosp, M, N, K, K, blockIdx.x, blockIdx.y, 0, lds,
                                    [&] { ln_panel<BF16, E>(ln, m0, M, panel); }, panel);
 }
 
@@ -1443,6 +1451,28 @@ int gemm_bf16_stored(int M, int N, int K, int batch, const uint16_t* A, long lon
                K, st);
 }
 
+// Whether the 32 x 32 tile's register groups hold two chunks (`wgs` workgroups, a contraction
+// of K in each; strided: an operand is k-strided).  Time in groups of two over groups of one,
+// both operands k-contiguous | both k-strided, at K = 512, 1024, 4096:
+//   workgroups          FP32                                  bfloat16
+//      256     1.03 1.02 0.91 | 1.00 0.99 0.95     1.03 1.05 0.88 | 0.94 0.91 0.87
+//      512     0.96 1.03 1.11 | 0.91 0.97 1.18     1.00 1.04 1.03 | 0.95 0.95 1.02
+//      768     1.12 1.16 1.16 | 1.08 0.91 0.99     1.20 1.14 1.01 | 1.04 1.03 0.99
+//     1024     0.90 0.89 0.79 | 0.93 0.94 0.99     1.19 1.13 1.01 | 1.03 1.02 0.96
+//     1536     1.04 1.02 1.00 | 0.96 0.96 0.97     1.25 1.16 1.02 | 1.08 1.07 0.89
+// One workgroup a compute unit has room for the deeper groups, which pay where a chunk's
+// loads are many (k-strided: 16 a lane) or the contraction long.  With more workgroups the
+// third that fits beside two counts for more; except in FP32 between three and four a
+// compute unit, which are two rounds either way (evenly filled in groups of two), and on
+// long k-strided contractions.
+static bool two_chunks(int bf16, long long wgs, int K, bool strided) {
+  if (wgs <= 256) return strided || K > 2048;
+  if (wgs <= 512) return strided && K <= (bf16 ? 2048 : 1024);
+  if (bf16) return strided && K >= 4096;
+  if (wgs <= 768) return strided && K >= 2048;
+  return K >= (wgs <= 1024 ? 256 : 512) && (strided || wgs <= 1216);
+}
+
 template <bool BF16, int AV, int BV>
 static int run_r(int M, int N, int K, int batch, const MatArg& A, const MatArg& B, const StMat& out, float* scratch,
                  size_t scratch_floats, hipStream_t st) {
@@ -1456,11 +1486,14 @@ static int run_r(int M, int N, int K, int batch, const MatArg& A, const MatArg& 
   const RMat a = rmat(A), b = rmat(B);
   StPart sp{scratch, M, N, splits};
   dim3 grid(cdiv(M, kTile), cdiv(N, kTile), batch * splits);
+  const bool two = two_chunks(BF16, (long long)grid.x * grid.y * grid.z, splits > 1 ? kchunk : K, !AV || !BV);
   if (splits <= 1) {
-    k_gemm_r<BF16, AV, BV, StMat, false><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
+    if (two) k_gemm_r<BF16, AV, BV, StMat, false, 2><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
+    else k_gemm_r<BF16, AV, BV, StMat, false><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
     return launch_status("gemm");
   }
-  k_gemm_r<BF16, AV, BV, StMat, true><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
+  if (two) k_gemm_r<BF16, AV, BV, StMat, true, 2><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
+  else k_gemm_r<BF16, AV, BV, StMat, true><<<grid, kThreads, 0, st>>>(a, b, out, sp, M, N, K, kchunk);
   SQ_TRY(launch_status("gemm_split"));
   const long long total = (long long)M * N * batch;
   k_split_reduce<StMat><<<cdiv(total, 256), 256, 0, st>>>(sp, out, batch);

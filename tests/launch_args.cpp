@@ -13,9 +13,11 @@ using namespace sq;
 // argument (a struct larger than that).
 static const void* g_wanted = nullptr;
 static int g_launches = 0, g_found = 0;
-static dim3 g_grid;   // of the last launch
+static dim3 g_grid;                    // of the last launch
+static const void* g_kernel = nullptr;
 
-extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
+extern "C" hipError_t hipLaunchKernel(const void* kernel, dim3, dim3, void** args, size_t, hipStream_t) {
+  g_kernel = kernel;
   ++g_launches;
   for (size_t o = 0; o + sizeof(void*) <= 96; o += sizeof(void*))
     if (g_wanted && memcmp((const char*)args[0] + o, &g_wanted, sizeof(void*)) == 0) ++g_found;
@@ -102,6 +104,34 @@ static bool tile_lines() {
   return ok;
 }
 
+// the kernel that a product of Z x 512 x 512 x K runs on (256 Z workgroups of the 32 x 32 tile)
+static const void* kernel(int bf16, int Z, int K, bool strided) {
+  float* p = LnCall::pre();   // not read
+  const int N = 512, ld = (K + 3) / 4 * 4;
+  const MatArg A{p, strided ? 1 : ld, strided ? N : 1, (long long)ld * N};
+  g_launches = 0;
+  const int s = gemm(bf16, N, N, K, Z, A, A, OutArg{p, N, (long long)N * N, nullptr, 0, 0, 0}, nullptr, 0, nullptr);
+  return s == SQ_OK && g_launches == 1 && g_grid.x == 16 ? g_kernel : nullptr;
+}
+
+static bool register_groups() {
+  // {bfloat16, strided, Z, K, Z, K, one kernel} across the lines between groups of one and two chunks
+  const int want[][7] = {{0, 0, 1, 2048, 1, 2049, 0}, {1, 0, 1, 2048, 1, 2049, 0}, {0, 1, 1, 64, 1, 4096, 1},
+                         {0, 1, 2, 1024, 2, 1025, 0}, {1, 1, 2, 2048, 2, 2049, 0}, {0, 0, 2, 64, 2, 4096, 1},
+                         {0, 1, 3, 2047, 3, 2048, 0}, {1, 1, 3, 4095, 3, 4096, 0}, {1, 0, 3, 64, 3, 4096, 1},
+                         {0, 1, 4, 255, 4, 256, 0},   {0, 1, 5, 511, 5, 512, 0},   {0, 0, 5, 511, 5, 512, 1},
+                         {0, 1, 1, 512, 2, 512, 1},   {0, 1, 2, 512, 3, 512, 0}};
+  bool ok = true;
+  for (const auto& w : want) {
+    const void* a = kernel(w[0], w[2], w[3], w[1]);
+    const void* b = kernel(w[0], w[4], w[5], w[1]);
+    const bool good = a && b && (a == b) == (w[6] != 0);
+    if (!good) printf("bf16 %d strided %d: %d x K %d and %d x K %d\n", w[0], w[1], w[2], w[3], w[4], w[5]);
+    ok = ok && good;
+  }
+  return ok;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "adam_average")) return ema_handed(0) && ema_handed(7) ? 0 : 1;
@@ -117,6 +147,7 @@ int main(int argc, char** argv) {
     return ln_form_refused(rows) && ln_form_refused(width) && ln_form_refused(strided) && !wide.launches(true) ? 0 : 1;
   }
   if (!strcmp(what, "tile_lines")) return tile_lines() ? 0 : 1;
+  if (!strcmp(what, "register_groups")) return register_groups() ? 0 : 1;
   printf("unknown check '%s'\n", what);
   return 2;
 }

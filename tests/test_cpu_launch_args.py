@@ -26,8 +26,9 @@ def program(tmp_path_factory):
 # adam: the target is a pointer that the kernel may read only where the average has elements.
 # ln: the products that normalise their own input refuse buffers that keep no FP32 values,
 # and the forms that they are not built for.  tile_lines: from where a product runs on the
-# 64 x 64 tile (just above one tile a compute unit it is the slower one).
+# 64 x 64 tile (just above one tile a compute unit it is the slower one).  register_groups:
+# where the 32 x 32 tile's groups hold two chunks.
 @pytest.mark.parametrize("check", ["adam_average", "adam_empty_average", "ln_dropped_weights", "ln_dropped_input",
-                                   "ln_forms", "tile_lines"])
+                                   "ln_forms", "tile_lines", "register_groups"])
 def test_launch_arguments(program, check):
     assert subprocess.run([program, check], timeout=60).returncode == 0

@@ -542,19 +542,25 @@ struct EncFwdArgs {
 
 // One image's source, requested a whole image ahead of its use.  Frames (SQK x SQK
 // blocks of uint8 HWC pixels, or the block means stored in a ring, SQK = 1) are read as
-// consecutive 16-byte chunks and go through LDS, where thread p sums pixel p's block:
+// consecutive 16-byte chunks (at the alignment the frames come with: 4 bytes raw, any of
+// a ring's) and go through LDS, where thread p sums pixel p's block:
 // reading the block rows (36 bytes a lane at SQK = 4) straight from memory costs each
 // load instruction some 40 cache lines.
+typedef unsigned v4u_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef unsigned v4u_words __attribute__((ext_vector_type(4), aligned(4)));
 template <int C, int SD, int NT, int SQK>
 struct EncImage {
   static constexpr int NB = SD * SQK * SD * SQK * C / 16;   // 16-byte chunks of a frame
   static constexpr int R = (NB + NT - 1) / NT, LDS = 16 * NB;
+  static constexpr int ALIGN = SQK == 1 ? 1 : 4;
   v4u v[R];
   __device__ __forceinline__ void load(const uint8_t* __restrict__ frame) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       const int c = (int)threadIdx.x + NT * i;
-      v[i] = reinterpret_cast<const v4u*>(frame)[NB % NT == 0 || c < NB ? c : NB - 1];
+      const uint8_t* p = frame + 16 * (NB % NT == 0 || c < NB ? c : NB - 1);
+      if constexpr (ALIGN == 1) v[i] = *reinterpret_cast<const v4u_any*>(p);
+      else v[i] = *reinterpret_cast<const v4u_words*>(p);
     }
   }
   __device__ __forceinline__ void store(uint8_t* buf) const {
@@ -1237,11 +1243,12 @@ int encoder_fused_fwd(int bf16, int C, int F, int n_conv, int side, const float*
 }
 
 // the frame forms' geometry: 64 x 64 x 9 frames squinted 4x (k = 4), or their 16 x 16
-// block means stored in a ring (k = 1), into the 16 x 16 encoder; frames read 16 bytes at
-// a time
+// block means stored in a ring (k = 1), into the 16 x 16 encoder, at any alignment that
+// EncImage reads
 static bool frames_ok(const uint8_t* frames, int H, int W, int C, int F, int n_conv, int k) {
-  return C == 9 && F == 32 && n_conv == 3 && ((k == 4 && H == 64 && W == 64) || (k == 1 && H == 16 && W == 16)) &&
-         (uintptr_t)frames % 16 == 0;
+  if (C != 9 || F != 32 || n_conv != 3) return false;
+  if (k == 4 && H == 64 && W == 64) return (uintptr_t)frames % EncImage<9, 16, 256, 4>::ALIGN == 0;
+  return k == 1 && H == 16 && W == 16;
 }
 
 static EncFwdArgs frame_args(int n, int nsave, const float* wp, const float* const* b, float* const* h,

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "common.h"
+#include "kernels/sample.h"
 
 using namespace sq;
 
@@ -132,6 +133,18 @@ static bool register_groups() {
   return ok;
 }
 
+// whether the encoder's launch reads frames `off` bytes off their alignment (k = 4: raw, k = 1: a ring's)
+static bool frames_read(int k, int off) {
+  const uint8_t* f = (const uint8_t*)LnCall::pre() + off;   // not read
+  const float* b[3] = {};
+  float* h[3] = {};
+  SampleArgs sa{};
+  sa.B = 2;
+  g_launches = 0;
+  const int s = encoder_fused_fwd_squint(sa, f, f, 16 * k, 16 * k, 9, 32, 3, k, nullptr, nullptr, b, h, nullptr, nullptr);
+  return s == SQ_OK && g_launches == 1;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "adam_average")) return ema_handed(0) && ema_handed(7) ? 0 : 1;
@@ -148,6 +161,16 @@ int main(int argc, char** argv) {
   }
   if (!strcmp(what, "tile_lines")) return tile_lines() ? 0 : 1;
   if (!strcmp(what, "register_groups")) return register_groups() ? 0 : 1;
+  if (!strcmp(what, "frame_alignment")) {
+    const int want[][3] = {{4, 0, 1}, {4, 4, 1}, {4, 12, 1}, {4, 2, 0}, {1, 0, 1}, {1, 1, 1}, {1, 6, 1}};
+    bool ok = true;
+    for (const auto& w : want) {
+      const bool read = frames_read(w[0], w[1]);
+      if (read != (w[2] != 0)) printf("k = %d, %d bytes off: %d\n", w[0], w[1], read);
+      ok = ok && read == (w[2] != 0);
+    }
+    return ok ? 0 : 1;
+  }
   printf("unknown check '%s'\n", what);
   return 2;
 }

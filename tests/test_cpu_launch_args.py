@@ -27,8 +27,10 @@ def program(tmp_path_factory):
 # ln: the products that normalise their own input refuse buffers that keep no FP32 values,
 # and the forms that they are not built for.  tile_lines: from where a product runs on the
 # 64 x 64 tile (just above one tile a compute unit it is the slower one).  register_groups:
-# where the 32 x 32 tile's groups hold two chunks.
+# where the 32 x 32 tile's groups hold two chunks.  frame_alignment: the update's encoder launch
+# reads raw frames at any word, a ring's at any byte.
 @pytest.mark.parametrize("check", ["adam_average", "adam_empty_average", "ln_dropped_weights", "ln_dropped_input",
-                                   "ln_forms", "tile_lines", "register_groups"])
+                                   "ln_forms", "tile_lines", "register_groups",
+                                   "frame_alignment"])
 def test_launch_arguments(program, check):
     assert subprocess.run([program, check], timeout=60).returncode == 0

@@ -8,8 +8,8 @@
 // per-lane base (its pixel or filter) plus an offset that depends on k alone, read
 // from a small LDS table, so v_mfma_f32_16x16x4_f32 (32 cycles) is the bound: 28,000
 // matrix-core cycles an image forward, 59,000 backward.  Measured for 250 images
-// (one per compute unit) against the general path: forward 26.7 us (90), backward with
-// the sum of the partial gradients 60.0 us (478).
+// (one per compute unit) against the general path: forward 26.2 us (90), backward with
+// the sum of the partial gradients 58.5 us (478).
 //
 // Forward: the sums are those of the general convolution, bit for bit (k = (c, tap) in
 // slices of 64, four accumulators taking 16 k of a slice each, added in order), so

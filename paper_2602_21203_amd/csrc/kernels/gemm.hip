@@ -6,7 +6,8 @@
 // (row, k) to memory, so transposes, concatenated inputs, im2col patches and the
 // ReLU mask of a convolution's gradient are all folded into the tile loads.
 //
-// Tiling: a 256-thread workgroup owns a 32 x 32 output tile.  Each K step stages
+// Tiling: a 256-thread workgroup owns a 32 x 32 output tile (large products of plain
+// matrices: 64 x 64, gemm_big.h, bit for bit the same results).  Each K step stages
 // a 32 x BK slice of both operands in LDS (converted to the compute type: FP32,
 // or bfloat16 rounded to nearest even), and the four waves each contract a
 // quarter of the slice (16 k for FP32 with v_mfma_f32_16x16x4_f32, 32 k for
@@ -412,8 +413,9 @@ __global__ __launch_bounds__(kThreads) void k_gemm(FA fa, FB fb, ST st, StPart s
 // multiplied.  Groups of one chunk let a compute unit hold three workgroups, of two, by
 // their registers and LDS, two (actor of 1,000 rows in FP32, its largest pair 21.2 against
 // 27.4 us; critic of 512 rows in bfloat16 99.7 against 103.0 us of kernels): two_chunks()
-// says which.  The four partial tiles are summed through LDS in a fixed order at the end.  bfloat16 operands are rounded to nearest even
-// (v_cvt_pk_bf16_f32) on the way to LDS or to the fragment.
+// says which.  The four partial tiles are summed through LDS in a fixed order at the end.
+// bfloat16 operands are rounded to nearest even (v_cvt_pk_bf16_f32) on the way to LDS or
+// to the fragment.
 struct RMat {
   const float* p; long long lr, lk, sz;
   const float* alt; int zalt, zdiv;   // batch groups, as MatArg
@@ -507,9 +509,10 @@ __device__ __forceinline__ void rload(const ROp& m, float (&raw)[16], int r0, in
   }
 }
 
-// raw chunk -> MFMA fragments (V = 2: of the panel, from its column k).  V = 1 goes through the wave's LDS tile in two
-// steps, so that the LDS round trips of a whole register group overlap: stage()
-// writes the chunk, frag() reads the fragments back after the group's single wait.
+// raw chunk -> MFMA fragments (V = 2: of the panel, from its column k).  V = 1 goes
+// through the wave's LDS tile in two steps, so that the LDS round trips of a whole
+// register group overlap: stage() writes the chunk, frag() reads the fragments back
+// after the group's single wait.
 template <bool BF16, int V>
 __device__ __forceinline__ void stage(const float (&raw)[16], typename RLds<BF16>::T* tile, int lane) {
   using LL = RLds<BF16>;
@@ -1531,9 +1534,10 @@ int gemm(int bf16, int M, int N, int K, int batch, MatArg A, MatArg B, OutArg C,
 }
 
 // Up to here a wave normalises its rows of a tile in one flight.  A policy query with
-// three separate LayerNorm launches / normalising in the products, bfloat16 and FP32, us:
-//   1 row    37.7 / 26.3   56.0 / 47.4        32 rows  38.5 / 41.4   61.8 / 65.0
-//   8 rows   37.9 / 28.7   59.1 / 51.8       512 rows  43.9 / 48.2   68.7 / 75.9
+// three separate LayerNorm launches / normalising in the products, us:
+//   rows         1            8            16           17           24           32
+//   bfloat16  33.4 / 25.2  34.9 / 27.6  35.9 / 31.7  36.3 / 34.2  36.7 / 36.5  37.7 / 40.5
+//   FP32      52.8 / 44.5  56.4 / 48.7  57.4 / 52.7  57.8 / 55.0  58.2 / 57.5  59.0 / 61.4
 constexpr int kLnGemmRows = 16;
 
 bool gemm_ln_ok(const LnIn& x, int n) {

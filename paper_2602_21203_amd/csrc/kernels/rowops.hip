@@ -846,10 +846,10 @@ int target_mse(const float* logits4, int B, const float* reward, const float* do
 // b_j are non-decreasing in j when gamma (1 - d) >= 0 (every step from z_j to b_j is
 // monotone, and so is its rounding), so the atoms with a weight at i are one run; the
 // others add +-0, which changes no finite sum.  A lane finds the run's start by
-// bisection and walks it, eight atoms read at a time: 2 to 3 atoms off the ends of the support against all N
-// (3,000 rows of 101 atoms: 6.9 us, all N atoms 13.0).  A row of a negative gamma or
-// with a probability that is not finite (whose products with zero weights are NaN)
-// walks all N.
+// bisection and walks it, eight atoms read at a time: 2 to 3 atoms off the ends of the
+// support against all N (3,000 rows of 101 atoms: 6.9 us, all N atoms 13.0).  A row of a
+// negative gamma or with a probability that is not finite (whose products with zero
+// weights are NaN) walks all N.
 template <int T>
 __global__ __launch_bounds__(256) void k_project(const float* __restrict__ p, const float* __restrict__ reward,
                                                  const uint8_t* __restrict__ done, const float* __restrict__ bonus,

@@ -1,7 +1,8 @@
 // encoder_fwd_noalloc: the encoder forward of encoder_fwd for callers that
 // cannot allocate (code under graph capture, tight serving loops).  Its scratch
-// -- the fused encoder's rearranged weights and the inner layers' activations --
-// lives in one file-scope device array of fixed size instead of a workspace.
+// -- the fused encoder's rearranged weights and the inner layers' activations,
+// which the bfloat16 fused form keeps in LDS instead -- lives in one file-scope
+// device array of fixed size instead of a workspace.
 //
 // The array's name is only a host-side stand-in in host code; its device
 // address is looked up once per device (with that device current) and kept,
@@ -45,7 +46,9 @@ int scratch_ptr(char** out) {
 }
 
 // the inner layers' activations and the fused path's rearranged weights (the
-// last layer is written straight into the caller's feature buffer)
+// last layer is written straight into the caller's feature buffer).  The bfloat16
+// fused form does not use the former; they count all the same, so that both
+// precisions take as many images.
 size_t plan(const sq::Net& net, int n, char* base, sq::EncBufs* e, int bf16) {
   const sq_dims& d = net.d;
   sq::Bump b{base};
